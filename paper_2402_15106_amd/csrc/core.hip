@@ -239,11 +239,19 @@ extern "C" const char* dsmp_last_error(const dsmp_handle* h) { return h ? h->err
 
 // ------------------------------------------------------------------ sampling
 //
-// Selection of the s smallest SplitMix64 keys out of M by a 4-pass MSB-first
-// radix select over 16-bit digits (the keys are recomputed every pass), then a
-// stable compaction of the candidates whose key is <= the s-th smallest.  The
-// keys are distinct (the mix is a bijection of the counter), so exactly s are
-// kept.
+// Selection of the s smallest SplitMix64 keys out of M by an MSB-first radix
+// select (the keys are recomputed, never stored), then a stable compaction of
+// the candidates whose key is at most the threshold.  The keys are distinct
+// (the mix is a bijection of the counter), so exactly s are kept.  Three forms
+// by M, each bounded by the latency of its launches rather than by traffic:
+//   M <= 8,192        one workgroup does everything in one launch
+//                     (1,024 of 4,096: eleven launches of 56 us -> 7.2 us)
+//   M <= 8,388,608    four launches (262,144 of 764,077: 95 -> 34 us): an 11-bit histogram, then one pass that
+//                     counts the sure candidates and lists those in the
+//                     threshold's bin (M / 2,048 on average), whose last
+//                     workgroup ranks the list; then the compaction
+//   larger M          four 16-bit digits, each a histogram and a pick (the
+//                     list of a bin would no longer be short)
 
 namespace {
 
@@ -371,15 +379,201 @@ __global__ __launch_bounds__(1024) void k_sel_count(int64_t M, uint64_t seed, co
   if (threadIdx.x == 0) cnt[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(1024) void k_sel_write(int64_t M, uint64_t seed, const SelState* st,
+__global__ __launch_bounds__(1024) void k_sel_write(int64_t M, uint64_t seed, const unsigned long long* threshold,
                                                     const uint32_t* __restrict__ off,
                                                     int32_t* __restrict__ out) {
   __shared__ uint32_t sh[32];
   int64_t i = (int64_t)blockIdx.x * SAMPLE_CHUNK + threadIdx.x;
-  uint32_t f = (i < M && splitmix64(seed, (uint64_t)i) <= st->prefix) ? 1u : 0u;
+  uint32_t f = (i < M && splitmix64(seed, (uint64_t)i) <= *threshold) ? 1u : 0u;
   uint32_t tot;
   uint32_t ex = block_exclusive_scan_1024(f, sh, &tot);
   if (f) out[off[blockIdx.x] + ex] = (int32_t)i;
+}
+
+// ---- one workgroup, and the middle form
+
+constexpr int SEL_SMALL = 8192;           // candidates of the one-workgroup form (8 per thread)
+constexpr int64_t SEL_MID = 1ll << 23;    // candidates of the middle form (a bin holds 4,096 on average)
+constexpr int SEL_DIG = 11, SEL_DBINS = 1 << SEL_DIG;
+constexpr int SEL_LIST = 16384;           // entries of the middle form's list
+constexpr int SEL_GRID = 128;             // most workgroups of its passes (each ends in a fence and an atomic)
+
+struct SelMid {                  // state of the middle form
+  unsigned long long threshold;  // the kept keys are those at most this
+  unsigned rank, bin;            // 1-based rank within bin `bin` of the top digit
+  unsigned listed;               // candidates of that bin
+  unsigned done1, done2;         // workgroups finished with each pass
+};
+
+struct SelLds {
+  uint32_t hist[SEL_DBINS];
+  uint32_t scan[32];
+  uint32_t found[3];             // digit, candidates before it, candidates in it
+};
+
+// The digit whose bin holds the rank-th candidate (1-based), from the
+// histogram in LDS: two bins per thread, one scan over the workgroup.
+__device__ __forceinline__ void block_pick(SelLds& L, uint32_t rank) {
+  const int t = threadIdx.x;
+  const uint32_t c0 = L.hist[2 * t], c1 = L.hist[2 * t + 1];
+  uint32_t tot;
+  const uint32_t ex = block_exclusive_scan_1024(c0 + c1, L.scan, &tot);
+  if (ex < rank && rank <= ex + c0) {
+    L.found[0] = 2 * t; L.found[1] = ex; L.found[2] = c0;
+  } else if (ex + c0 < rank && rank <= ex + c0 + c1) {
+    L.found[0] = 2 * t + 1; L.found[1] = ex + c0; L.found[2] = c1;
+  }
+  __syncthreads();
+}
+
+// The rank-th smallest of the keys key(0 .. n-1) that agree with `prefix` in
+// their top `fixed` bits, by one workgroup of 1,024 threads: a digit at a
+// time, until every candidate left is kept.  Returns a threshold T: exactly
+// `rank` of those keys are at most T.  (The digits run out after 64 bits at
+// the latest, when one key is left, since the keys are distinct.)
+template <typename KeyFn>
+__device__ uint64_t block_select(SelLds& L, int64_t n, KeyFn key, uint64_t prefix, int fixed, uint32_t rank) {
+  for (;;) {
+    const int dig = 64 - fixed < SEL_DIG ? 64 - fixed : SEL_DIG, shift = 64 - fixed - dig;
+    for (int b = threadIdx.x; b < SEL_DBINS; b += 1024) L.hist[b] = 0;
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < n; i += 1024) {
+      const uint64_t k = key(i);
+      if (fixed == 0 || (k ^ prefix) >> (64 - fixed) == 0)
+        atomicAdd(&L.hist[(k >> shift) & ((1u << dig) - 1u)], 1u);
+    }
+    __syncthreads();
+    block_pick(L, rank);
+    const uint32_t d = L.found[0], cnt = L.found[2];
+    rank -= L.found[1];
+    prefix |= (uint64_t)d << shift;
+    fixed += dig;
+    if (rank == cnt || fixed == 64) return prefix | (shift ? (1ull << shift) - 1ull : 0ull);
+    __syncthreads();   // found[] is read before the next digit writes it
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_sel_small(int M, uint32_t s, uint64_t seed, int32_t* __restrict__ out) {
+  __shared__ SelLds L;
+  const uint64_t T = block_select(L, M, [&](int64_t i) { return splitmix64(seed, (uint64_t)i); }, 0, 0, s);
+  constexpr int PER = SEL_SMALL / 1024;
+  const int i0 = threadIdx.x * PER;
+  uint32_t keep = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (i0 + u < M && splitmix64(seed, (uint64_t)(i0 + u)) <= T) keep |= 1u << u;
+  uint32_t tot;
+  __syncthreads();
+  uint32_t at = block_exclusive_scan_1024(__popc(keep), L.scan, &tot);
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (keep >> u & 1u) out[at++] = i0 + u;
+}
+
+__global__ __launch_bounds__(1024) void k_mid_init(SelMid* st, uint32_t* hist) {
+  if (threadIdx.x == 0) *st = SelMid{};
+  for (int b = threadIdx.x; b < SEL_DBINS; b += 1024) hist[b] = 0;
+}
+
+// Whether this workgroup is the last of the grid to get here.  What the
+// others wrote before it is then visible to agent-scope loads.  One thread
+// fences for its workgroup, after the barrier has completed the workgroup's
+// writes (a fence by every thread is a write-back of the L2 by every wave:
+// k_mid_list at 764,077 candidates takes 182 us with it and 746 workgroups, 31
+// with one fence each, 16 with at most SEL_GRID workgroups).
+__device__ __forceinline__ bool last_block(unsigned* counter) {
+  __shared__ unsigned last;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    last = atomicAdd(counter, 1u) == gridDim.x - 1;
+    __threadfence();
+  }
+  __syncthreads();
+  return last != 0;
+}
+
+__device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// First pass: the histogram of the top digit, each workgroup's in LDS first
+// (few workgroups, so that the merge is few atomics); the last one picks the
+// digit that holds the s-th key.
+__global__ __launch_bounds__(1024) void k_mid_hist(int64_t M, uint32_t s, uint64_t seed, SelMid* st, uint32_t* hist) {
+  __shared__ SelLds L;
+  for (int b = threadIdx.x; b < SEL_DBINS; b += 1024) L.hist[b] = 0;
+  __syncthreads();
+  const int64_t stride = (int64_t)gridDim.x * 1024;
+  for (int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x; i < M; i += stride)
+    atomicAdd(&L.hist[splitmix64(seed, (uint64_t)i) >> (64 - SEL_DIG)], 1u);
+  __syncthreads();
+  for (int b = threadIdx.x; b < SEL_DBINS; b += 1024)
+    if (L.hist[b]) atomicAdd(&hist[b], L.hist[b]);
+  if (!last_block(&st->done1)) return;
+  for (int b = threadIdx.x; b < SEL_DBINS; b += 1024) L.hist[b] = load_agent(hist + b);
+  __syncthreads();
+  block_pick(L, s);
+  if (threadIdx.x == 0) {
+    st->bin = L.found[0];
+    st->rank = s - L.found[1];
+  }
+}
+
+// Second pass, by chunks of SAMPLE_CHUNK candidates: the count
+// of those below the threshold's bin, and the ones in it to the list.  The
+// last workgroup ranks the list, adds its kept ones to their chunks' counts
+// and scans the counts.  A list that overflowed (a bin of four times its
+// expected size at least) is ranked from the keys themselves.
+__global__ __launch_bounds__(1024) void k_mid_list(int64_t M, uint64_t seed, SelMid* st, uint32_t* __restrict__ list,
+                                                   uint32_t* cnt, int nb) {
+  __shared__ SelLds L;
+  __shared__ uint32_t below;
+  const uint32_t bin = st->bin;
+  for (int c = blockIdx.x; c < nb; c += gridDim.x) {
+    if (threadIdx.x == 0) below = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)c * SAMPLE_CHUNK + threadIdx.x;
+    const uint32_t d = i < M ? (uint32_t)(splitmix64(seed, (uint64_t)i) >> (64 - SEL_DIG)) : ~0u;
+    const uint64_t lt = __ballot(d < bin);
+    if ((threadIdx.x & 63) == 0 && lt) atomicAdd(&below, (uint32_t)__popcll(lt));
+    if (d == bin) {
+      const uint32_t at = atomicAdd(&st->listed, 1u);
+      if (at < SEL_LIST) __hip_atomic_store(list + at, (uint32_t)i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(cnt + c, below, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (!last_block(&st->done2)) return;
+  const uint32_t listed = load_agent(&st->listed), rank = st->rank;
+  const uint64_t prefix = (uint64_t)bin << (64 - SEL_DIG);
+  auto key_of = [&](int64_t c) { return splitmix64(seed, (uint64_t)c); };
+  uint64_t T;
+  if (listed <= SEL_LIST) {
+    T = block_select(L, listed, [&](int64_t e) { return key_of(load_agent(list + e)); }, prefix, SEL_DIG, rank);
+    for (uint32_t e = threadIdx.x; e < listed; e += 1024) {
+      const uint32_t c = load_agent(list + e);
+      if (key_of(c) <= T) atomicAdd(&cnt[c / SAMPLE_CHUNK], 1u);
+    }
+  } else {
+    T = block_select(L, M, key_of, prefix, SEL_DIG, rank);
+    for (int64_t c = threadIdx.x; c < M; c += 1024) {
+      const uint64_t k = key_of(c);
+      if (k >> (64 - SEL_DIG) == bin && k <= T) atomicAdd(&cnt[c / SAMPLE_CHUNK], 1u);
+    }
+  }
+  if (threadIdx.x == 0) st->threshold = T;
+  __threadfence();
+  __syncthreads();
+  uint32_t carry = 0;
+  for (int b0 = 0; b0 < nb; b0 += 1024) {
+    const int b = b0 + threadIdx.x;
+    const uint32_t v = b < nb ? load_agent(cnt + b) : 0u;
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan_1024(v, L.scan, &tot);
+    if (b < nb) cnt[b] = carry + ex;
+    carry += tot;
+  }
 }
 
 __global__ void k_iota(int32_t* out, int64_t n) {
@@ -418,6 +612,24 @@ dsmp_status sample_run(dsmp_handle* h, int64_t M, int64_t s, uint64_t seed, int3
   uint32_t* hist = c.take<uint32_t>(SEL_BINS);
   int nb = (int)ceil_div(M, SAMPLE_CHUNK);
   uint32_t* cnt = c.take<uint32_t>(nb + 2);
+  if (M <= SEL_SMALL) {
+    hipLaunchKernelGGL(k_sel_small, dim3(1), dim3(1024), 0, h->stream, (int)M, (uint32_t)s, seed, idx_out);
+    DSMP_LAUNCHED(h, "sample");
+    return DSMP_OK;
+  }
+  if (M <= SEL_MID) {
+    // state, histogram and list in the room of the large form's histogram
+    SelMid* ms = reinterpret_cast<SelMid*>(hist);
+    uint32_t *mh = hist + 64, *list = hist + 64 + SEL_DBINS;
+    static_assert(sizeof(SelMid) <= 256 && 64 + SEL_DBINS + SEL_LIST <= SEL_BINS, "fits the histogram's room");
+    hipLaunchKernelGGL(k_mid_init, dim3(1), dim3(1024), 0, h->stream, ms, mh);
+    hipLaunchKernelGGL(k_mid_hist, dim3(std::min(ceil_div(M, 4096), (unsigned)SEL_GRID)), dim3(1024), 0, h->stream, M, (uint32_t)s,
+                       seed, ms, mh);
+    hipLaunchKernelGGL(k_mid_list, dim3(std::min(nb, SEL_GRID)), dim3(1024), 0, h->stream, M, seed, ms, list, cnt, nb);
+    hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, seed, &ms->threshold, cnt, idx_out);
+    DSMP_LAUNCHED(h, "sample");
+    return DSMP_OK;
+  }
   // the state and the histogram are cleared by a kernel on every call
   hipLaunchKernelGGL(k_sel_init, dim3(SEL_BINS / 4 / 1024), dim3(1024), 0, h->stream, st, (uint64_t)s, hist);
   unsigned g = ceil_div(M, 256);
@@ -428,7 +640,7 @@ dsmp_status sample_run(dsmp_handle* h, int64_t M, int64_t s, uint64_t seed, int3
   }
   hipLaunchKernelGGL(k_sel_count, dim3(nb), dim3(1024), 0, h->stream, M, seed, st, cnt);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, h->stream, cnt, nb);
-  hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, seed, st, cnt, idx_out);
+  hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, seed, &st->prefix, cnt, idx_out);
   DSMP_LAUNCHED(h, "sample");
   return DSMP_OK;
 }
@@ -496,16 +708,34 @@ extern "C" dsmp_status dsmp_sample_nodes_noalloc(dsmp_handle* h, int64_t M, int6
 // ------------------------------------------------------------------ gather
 
 namespace {
-__global__ void k_gather_rows(const uint32_t* __restrict__ src, int64_t n_src_rows, int64_t words,
-                              const int32_t* __restrict__ idx, int64_t n, uint32_t* __restrict__ dst) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = n * words;
-  int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; t < total; t += stride) {
-    int64_t r = t / words, w = t - r * words;
-    int32_t s = idx[r];
-    dst[t] = (s >= 0 && s < n_src_rows) ? src[(int64_t)s * words + w] : 0u;
+// One thread per unit: a 16-byte unit where the rows and both arrays are
+// aligned to it, else a word.  Indices are 32-bit below 2^31 units (the row of
+// a unit is then one short division, a shift where a row is a power of two of
+// units).  Gathers of 262,144 rows of 12, 16 and 256 bytes: 42.6 -> 30.5 us
+// together, the last at 5.8 TB/s read and written (words with 64-bit divisions
+// before).
+template <typename U, typename I>
+__global__ __launch_bounds__(256) void k_gather_rows(const U* __restrict__ src, int64_t n_src_rows, I units, int sh,
+                                                     const int32_t* __restrict__ idx, I total, U* __restrict__ dst) {
+  for (I t = (I)blockIdx.x * 256 + threadIdx.x; t < total; t += (I)gridDim.x * 256) {
+    const I r = sh >= 0 ? t >> sh : t / units, w = t - r * units;
+    const int32_t s = idx[r];
+    dst[t] = (s >= 0 && s < n_src_rows) ? src[(int64_t)s * units + w] : U{};
   }
+}
+
+template <typename U>
+void gather_launch(hipStream_t st, const void* src, int64_t n_src_rows, int64_t row_bytes, const int32_t* idx,
+                   int64_t n, void* dst) {
+  const int64_t units = row_bytes / (int64_t)sizeof(U), total = n * units;
+  const int sh = (units & (units - 1)) == 0 ? __builtin_ctzll((unsigned long long)units) : -1;
+  const unsigned g = (unsigned)std::min<int64_t>((total + 255) / 256, 1 << 22);
+  if (total < (1ll << 31))   // a step past the end stays below 2^32
+    hipLaunchKernelGGL((k_gather_rows<U, uint32_t>), dim3(g), dim3(256), 0, st, static_cast<const U*>(src),
+                       n_src_rows, (uint32_t)units, sh, idx, (uint32_t)total, static_cast<U*>(dst));
+  else
+    hipLaunchKernelGGL((k_gather_rows<U, uint64_t>), dim3(g), dim3(256), 0, st, static_cast<const U*>(src),
+                       n_src_rows, (uint64_t)units, sh, idx, (uint64_t)total, static_cast<U*>(dst));
 }
 }  // namespace
 
@@ -517,12 +747,10 @@ extern "C" dsmp_status dsmp_gather_rows(dsmp_handle* h, const void* src, int64_t
   if (n == 0) return DSMP_OK;
   DSMP_CHECK(h, src && idx && dst, DSMP_INVALID_ARG, "gather pointer is NULL");
   ProfScope prof(h, DSMP_K_GATHER);
-  int64_t words = row_bytes / 4;
-  unsigned g = ceil_div(n * words, 256);
-  if (g > 8192) g = 8192;
-  hipLaunchKernelGGL(k_gather_rows, dim3(g), dim3(256), 0, h->stream,
-                     static_cast<const uint32_t*>(src), n_src_rows, words, idx, n,
-                     static_cast<uint32_t*>(dst));
+  const bool wide = row_bytes % 16 == 0 &&
+                    ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
+  if (wide) gather_launch<uint4>(h->stream, src, n_src_rows, row_bytes, idx, n, dst);
+  else gather_launch<uint32_t>(h->stream, src, n_src_rows, row_bytes, idx, n, dst);
   DSMP_LAUNCHED(h, "gather_rows");
   return DSMP_OK;
 }

@@ -25,6 +25,33 @@ def test_sampling_bit_exact(env, M, s, seed):
     assert np.array_equal(got, oracle.sampling.sample_nodes(M, s, seed))
 
 
+@pytest.mark.parametrize("M", [2, 1023, 8191, 8192, 8193, 4 << 20, (8 << 20) - 3, (8 << 20) + 1])
+def test_sampling_forms(env, M):
+    """The one-workgroup, list and four-digit forms at their bounds, with few,
+    half and nearly all candidates kept."""
+    dm, lib, torch = env
+    for s in sorted({1, M // 2, M - 1}):
+        announce("sample form", M, s)
+        got = lib.dsmp_sample_nodes(M, s, 1000 + s).cpu().numpy()
+        assert np.array_equal(got, oracle.sampling.sample_nodes(M, s, 1000 + s)), s
+
+
+@pytest.mark.parametrize("cols,offset", [(4, 0), (12, 0), (64, 0), (64, 1), (3, 0), (5, 2)])
+def test_gather_rows_units(env, cols, offset):
+    """16-byte and word units: row lengths, arrays off a 16-byte address, and
+    indices out of range (zero rows)."""
+    dm, lib, torch = env
+    announce("gather", cols, offset)
+    buf = torch.arange(offset + 50 * cols, dtype=torch.float32, device="cuda")
+    src = buf[offset:].view(50, cols)
+    idx = torch.tensor([49, -1, 0, 50, 7, 7], dtype=torch.int32, device="cuda")
+    out = torch.full((offset + 6 * cols,), -1.0, device="cuda")[offset:].view(6, cols)
+    lib.dsmp_gather_rows(src, idx, out=out)
+    ok = (idx >= 0) & (idx < 50)
+    want = torch.where(ok[:, None], src[idx.clamp(0, 49).long()], torch.zeros(1, device="cuda"))
+    assert torch.equal(out, want)
+
+
 def test_sampling_rejects_bad_sizes(env):
     dm, lib, torch = env
     with pytest.raises(dm.DsmpError) as ei:
