@@ -18,6 +18,10 @@ struct dsmp_handle {
   int edge_algo = 0;   // DSMP_EDGE_AUTO / PER_EDGE / AGGREGATE
   int n_cu = 256;      // compute units of the device (sizes persistent grids)
   void* sample_scratch = nullptr;   // device address of the allocation-free sampling scratch
+  // READBACK_BYTES of pinned host memory (allocated at creation) that kernels
+  // write small results to for the calls that synchronise, and its device address
+  void* readback = nullptr;
+  void* readback_dev = nullptr;
   std::string err;
   // kernel timing (opt-in)
   struct Mark {
@@ -109,9 +113,42 @@ struct Carve {
 
 inline unsigned ceil_div(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
+constexpr size_t READBACK_BYTES = 64;
+
+// Exclusive scan over a workgroup of 1,024 threads (sh: 32 words of LDS, free
+// again when it returns).
+__device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32_t* sh,
+                                                             uint32_t* total) {
+  // 1024 threads = 16 waves; wave scans by shuffles, then a scan of wave sums.
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) sh[wid] = x;
+  __syncthreads();
+  if (wid == 0) {
+    uint32_t s = lane < 16 ? sh[lane] : 0u;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      uint32_t y = __shfl_up(s, o, 64);
+      if (lane >= o) s += y;
+    }
+    if (lane < 16) sh[16 + lane] = s;
+  }
+  __syncthreads();
+  uint32_t wave_off = wid > 0 ? sh[16 + wid - 1] : 0u;
+  *total = sh[31];
+  uint32_t r = wave_off + x - v;
+  __syncthreads();
+  return r;
+}
+
 // Device-wide exclusive scan of n uint32 counts into out[0..n] (out[n] = total),
-// in three launches: per-block sums, a single-block scan of the sums, and the
-// per-block scan with offsets.  tmp needs scan_tmp_elems(n) uint32.
+// in one launch (up to 16,384), two (per-block sums, then per-block scans that
+// add up the sums ahead of them) or, above 4 M, three (a scan of the sums between).  tmp needs scan_tmp_elems(n) uint32.
 constexpr int SCAN_BLOCK = 1024;
 inline size_t scan_tmp_elems(int64_t n) { return (size_t)ceil_div(n, SCAN_BLOCK) + 1; }
 dsmp_status exclusive_scan_u32(dsmp_handle* h, const uint32_t* in, int32_t* out, int64_t n,

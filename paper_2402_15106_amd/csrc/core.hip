@@ -11,35 +11,6 @@ using namespace dsmp;
 
 namespace {
 
-__device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32_t* sh,
-                                                             uint32_t* total) {
-  // 1024 threads = 16 waves; wave scans by shuffles, then a scan of wave sums.
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sh[wid] = x;
-  __syncthreads();
-  if (wid == 0) {
-    uint32_t s = lane < 16 ? sh[lane] : 0u;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      uint32_t y = __shfl_up(s, o, 64);
-      if (lane >= o) s += y;
-    }
-    if (lane < 16) sh[16 + lane] = s;
-  }
-  __syncthreads();
-  uint32_t wave_off = wid > 0 ? sh[16 + wid - 1] : 0u;
-  *total = sh[31];
-  uint32_t r = wave_off + x - v;
-  __syncthreads();
-  return r;
-}
-
 __global__ __launch_bounds__(1024) void k_scan_blocksums(const uint32_t* __restrict__ in,
                                                          int64_t n, uint32_t* __restrict__ sums) {
   __shared__ uint32_t sh[32];
@@ -75,6 +46,26 @@ __global__ __launch_bounds__(1024) void k_scan_final(const uint32_t* __restrict_
   uint32_t ex = block_exclusive_scan_1024(v, sh, &tot);
   if (i < n) out[i] = (int32_t)(sums[blockIdx.x] + ex);
   if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = (int32_t)sums[nb];
+}
+
+// k_scan_final without the scan of the block sums before it: every block adds
+// up the sums ahead of it itself (at most SCAN_DIRECT of them, four loads per
+// thread), which is shorter than one more launch (286,000 values: 12.7 -> 8.6 us).
+constexpr int SCAN_DIRECT = 4096;
+__global__ __launch_bounds__(1024) void k_scan_direct(const uint32_t* __restrict__ in, int64_t n,
+                                                      const uint32_t* __restrict__ sums,
+                                                      int32_t* __restrict__ out) {
+  __shared__ uint32_t sh[32];
+  const int b = blockIdx.x;
+  const int64_t i = (int64_t)b * SCAN_BLOCK + threadIdx.x;
+  const uint32_t v = i < n ? in[i] : 0u;
+  uint32_t pre = 0;
+  for (int k = threadIdx.x; k < b; k += SCAN_BLOCK) pre += sums[k];
+  uint32_t before, tot;
+  block_exclusive_scan_1024(pre, sh, &before);
+  const uint32_t ex = block_exclusive_scan_1024(v, sh, &tot);
+  if (i < n) out[i] = (int32_t)(before + ex);
+  if (i == n - 1) out[n] = (int32_t)(before + tot);
 }
 
 // Exclusive scan of up to 16 * 1024 values by one workgroup in one launch:
@@ -131,6 +122,11 @@ dsmp_status exclusive_scan_u32(dsmp_handle* h, const uint32_t* in, int32_t* out,
     return DSMP_OK;
   }
   hipLaunchKernelGGL(k_scan_blocksums, dim3(nb), dim3(1024), 0, h->stream, in, n, tmp);
+  if (nb <= SCAN_DIRECT) {
+    hipLaunchKernelGGL(k_scan_direct, dim3(nb), dim3(1024), 0, h->stream, in, n, tmp, out);
+    DSMP_LAUNCHED(h, "scan");
+    return DSMP_OK;
+  }
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, h->stream, tmp, nb);
   hipLaunchKernelGGL(k_scan_final, dim3(nb), dim3(1024), 0, h->stream, in, n, tmp, out, nb);
   DSMP_LAUNCHED(h, "scan");
@@ -172,6 +168,14 @@ extern "C" dsmp_status dsmp_create(dsmp_handle** out, int device) {
     delete h;
     return st;
   }
+  void* dev = nullptr;
+  if (hipHostMalloc(reinterpret_cast<void**>(&h->readback), READBACK_BYTES, hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(&dev, h->readback, 0) != hipSuccess) {
+    if (h->readback) (void)hipHostFree(h->readback);
+    delete h;
+    return DSMP_HIP_ERROR;
+  }
+  h->readback_dev = dev;
   *out = h;
   return DSMP_OK;
 }
@@ -180,6 +184,7 @@ extern "C" dsmp_status dsmp_destroy(dsmp_handle* h) {
   if (!h) return DSMP_OK;
   for (auto& m : h->pending) { (void)hipEventDestroy(m.a); (void)hipEventDestroy(m.b); }
   for (auto& e : h->pool) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
+  if (h->readback) (void)hipHostFree(h->readback);
   delete h;
   return DSMP_OK;
 }
@@ -789,6 +794,55 @@ __global__ void k_sub_scatter(int64_t n, const uint32_t* __restrict__ own, const
   else if (ovl[i]) idx[own_pos[n] + ovl_pos[i]] = (int32_t)i;
 }
 
+// All of the selection for up to SUB_SMALL nodes by one workgroup: eight
+// consecutive nodes per thread, both counts scanned at once (16 bits each),
+// the two lists written and their lengths left in host memory.  One launch in
+// place of four and two copies (8,192 nodes: 30 us of kernels -> 8).
+constexpr int SUB_SMALL = 8192;
+__global__ __launch_bounds__(1024) void k_sub_small(const float* __restrict__ pos, int n, int D, Box b,
+                                                    int32_t* __restrict__ idx, int32_t* counts) {
+  __shared__ uint32_t sh[32];
+  constexpr int PER = SUB_SMALL / 1024;
+  const int i0 = threadIdx.x * PER;
+  uint32_t own = 0, ovl = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = i0 + u;
+    if (i < n) {
+      bool in = true, ext = true;
+      for (int a = 0; a < D; ++a) {
+        const float p = pos[i * D + a];
+        in = in && p >= b.lo[a] && p < b.hi[a];
+        ext = ext && p >= b.elo[a] && p < b.ehi[a];
+      }
+      own |= (in ? 1u : 0u) << u;
+      ovl |= (ext && !in ? 1u : 0u) << u;
+    }
+  }
+  uint32_t tot;
+  const uint32_t ex = block_exclusive_scan_1024((uint32_t)__popc(own) | (uint32_t)__popc(ovl) << 16, sh, &tot);
+  const int n_own = (int)(tot & 0xFFFFu), n_ovl = (int)(tot >> 16);
+  int at = (int)(ex & 0xFFFFu), bt = n_own + (int)(ex >> 16);
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (own >> u & 1u) idx[at++] = i0 + u;
+    if (ovl >> u & 1u) idx[bt++] = i0 + u;
+  }
+  if (threadIdx.x == 0) {
+    counts[0] = n_own;
+    counts[1] = n_ovl;
+    __threadfence_system();
+  }
+}
+
+// the lengths of the two lists, left in host memory
+__global__ void k_sub_counts(int64_t n, const int32_t* __restrict__ own_pos, const int32_t* __restrict__ ovl_pos,
+                             int32_t* counts) {
+  counts[0] = own_pos[n];
+  counts[1] = ovl_pos[n];
+  __threadfence_system();
+}
+
 __global__ void k_scatter_rows(const uint32_t* __restrict__ src, int64_t words, const int32_t* __restrict__ idx,
                                int64_t n, uint32_t* __restrict__ dst, int64_t n_dst_rows) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -850,18 +904,23 @@ extern "C" dsmp_status dsmp_subdomain_select(dsmp_handle* h, const float* pos, i
   }
   ProfScope prof(h, DSMP_K_GATHER);
   hipStream_t s = h->stream;
-  hipLaunchKernelGGL(k_sub_flags, dim3(ceil_div(n, 256)), dim3(256), 0, s, pos, n, (int)dim, b, w.own, w.ovl);
-  DSMP_LAUNCHED(h, "sub-domain flags");
-  dsmp_status st;
-  if ((st = exclusive_scan_u32(h, w.own, w.own_pos, n, w.tmp)) != DSMP_OK) return st;
-  if ((st = exclusive_scan_u32(h, w.ovl, w.ovl_pos, n, w.tmp)) != DSMP_OK) return st;
-  hipLaunchKernelGGL(k_sub_scatter, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, w.own, w.ovl, w.own_pos,
-                     w.ovl_pos, idx_out);
-  DSMP_LAUNCHED(h, "sub-domain scatter");
-  int32_t tot[2];
-  DSMP_HIP(h, hipMemcpyAsync(&tot[0], w.own_pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  DSMP_HIP(h, hipMemcpyAsync(&tot[1], w.ovl_pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  int32_t* counts = static_cast<int32_t*>(h->readback_dev);
+  if (n <= SUB_SMALL) {
+    hipLaunchKernelGGL(k_sub_small, dim3(1), dim3(1024), 0, s, pos, (int)n, (int)dim, b, idx_out, counts);
+    DSMP_LAUNCHED(h, "sub-domain selection");
+  } else {
+    hipLaunchKernelGGL(k_sub_flags, dim3(ceil_div(n, 256)), dim3(256), 0, s, pos, n, (int)dim, b, w.own, w.ovl);
+    DSMP_LAUNCHED(h, "sub-domain flags");
+    dsmp_status st;
+    if ((st = exclusive_scan_u32(h, w.own, w.own_pos, n, w.tmp)) != DSMP_OK) return st;
+    if ((st = exclusive_scan_u32(h, w.ovl, w.ovl_pos, n, w.tmp)) != DSMP_OK) return st;
+    hipLaunchKernelGGL(k_sub_scatter, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, w.own, w.ovl, w.own_pos,
+                       w.ovl_pos, idx_out);
+    hipLaunchKernelGGL(k_sub_counts, dim3(1), dim3(1), 0, s, n, w.own_pos, w.ovl_pos, counts);
+    DSMP_LAUNCHED(h, "sub-domain scatter");
+  }
   DSMP_HIP(h, hipStreamSynchronize(s));
+  const volatile int32_t* tot = static_cast<const int32_t*>(h->readback);
   *n_owned = tot[0];
   *n_total = (int64_t)tot[0] + tot[1];
   return DSMP_OK;

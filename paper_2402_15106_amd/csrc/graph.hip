@@ -48,9 +48,13 @@ __device__ __forceinline__ float dist2(float3 a, float3 b, int D) {
   return d2;
 }
 
+// The same launch clears the counters of the later passes (za[0..nza), zb[0..nzb)).
 __global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ pos, int64_t n, int D,
-                                                      float* __restrict__ part) {
+                                                      float* __restrict__ part, uint32_t* __restrict__ za, int64_t nza,
+                                                      uint32_t* __restrict__ zb, int64_t nzb) {
   __shared__ float sh[6][256];
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nza; i += (int64_t)gridDim.x * 256) za[i] = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nzb; i += (int64_t)gridDim.x * 256) zb[i] = 0;
   float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     float3 p = load_pos(pos, i, D);
@@ -70,26 +74,11 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ 
   if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = sh[threadIdx.x][0];
 }
 
-// One wave reduces the partial boxes, one lane chooses the cell size.  Cells are
-// at least r*(1 + 2^-10) wide, so two points that pass the float32 radius
-// test always sit in the same or adjacent cells (cell coordinates are formed
-// in double, see cell_coord); the grid is coarsened by doubling until it has
-// at most `cap` cells.
-__global__ void k_grid_setup(const float* __restrict__ part, int nb, int D, float r, int64_t cap,
-                             GridParams* __restrict__ g, GraphStats* __restrict__ st) {
-  const int lane = threadIdx.x;  // one wave
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = lane; b < nb; b += 64)
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = fminf(lo[a], part[b * 6 + a]);
-      hi[a] = fmaxf(hi[a], part[b * 6 + 3 + a]);
-    }
-  for (int o = 32; o > 0; o >>= 1)
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = fminf(lo[a], __shfl_xor(lo[a], o, 64));
-      hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], o, 64));
-    }
-  if (lane != 0) return;
+// Grid of the box [lo, hi].  Cells are at least r*(1 + 2^-10) wide, so two
+// points that pass the float32 radius test always sit in the same or adjacent
+// cells (cell coordinates are formed in double, see cell_coord); the grid is
+// coarsened by doubling until it has at most `cap` cells.
+__device__ __forceinline__ GridParams choose_grid(float lo[3], float hi[3], int D, float r, int64_t cap) {
   for (int a = D; a < 3; ++a) { lo[a] = 0.0f; hi[a] = 0.0f; }
   for (int a = 0; a < 3; ++a)
     if (!(hi[a] >= lo[a])) { lo[a] = 0.0f; hi[a] = 0.0f; }   // empty input
@@ -105,11 +94,29 @@ __global__ void k_grid_setup(const float* __restrict__ part, int nb, int D, floa
     if (cells <= (double)cap) break;
     c *= 2.0;
   }
-  for (int a = 0; a < 3; ++a) { g->lo[a] = lo[a]; g->dims[a] = (int)dims[a]; }
-  g->inv_c = 1.0 / c;
-  g->ncell = g->dims[0] * g->dims[1] * g->dims[2];
-  st->total = 0;
-  st->maxraw = 0;
+  GridParams g;
+  for (int a = 0; a < 3; ++a) { g.lo[a] = lo[a]; g.dims[a] = (int)dims[a]; }
+  g.inv_c = 1.0 / c;
+  g.ncell = g.dims[0] * g.dims[1] * g.dims[2];
+  return g;
+}
+
+// One wave reduces the partial boxes, one lane chooses the grid.
+__global__ void k_grid_setup(const float* __restrict__ part, int nb, int D, float r, int64_t cap,
+                             GridParams* __restrict__ g) {
+  const int lane = threadIdx.x;  // one wave
+  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  for (int b = lane; b < nb; b += 64)
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = fminf(lo[a], part[b * 6 + a]);
+      hi[a] = fmaxf(hi[a], part[b * 6 + 3 + a]);
+    }
+  for (int o = 32; o > 0; o >>= 1)
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = fminf(lo[a], __shfl_xor(lo[a], o, 64));
+      hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], o, 64));
+    }
+  if (lane == 0) *g = choose_grid(lo, hi, D, r, cap);
 }
 
 // Cell of coordinate v, in double: v - lo is exact there and the product
@@ -123,34 +130,127 @@ __device__ __forceinline__ int cell_coord(float v, float lo, double inv_c, int d
   return c < 0 ? 0 : (c >= dim ? dim - 1 : c);
 }
 
+__device__ __forceinline__ uint32_t cell_of(float3 p, const GridParams& g, int D) {
+  const int cx = cell_coord(p.x, g.lo[0], g.inv_c, g.dims[0]);
+  const int cy = cell_coord(p.y, g.lo[1], g.inv_c, g.dims[1]);
+  const int cz = D == 3 ? cell_coord(p.z, g.lo[2], g.inv_c, g.dims[2]) : 0;
+  return (uint32_t)(cx + g.dims[0] * (cy + g.dims[1] * cz));
+}
+
+// The count that a point finds in its cell is its place there, so that the
+// scatter needs no atomics of its own (285,564 points: 28 + 43 us -> 30 + 6).
 __global__ __launch_bounds__(256) void k_cell_hash(const float* __restrict__ pos, int64_t n, int D,
                                                    const GridParams* __restrict__ g,
-                                                   uint32_t* __restrict__ cellid,
+                                                   uint32_t* __restrict__ cellid, uint32_t* __restrict__ place,
                                                    uint32_t* __restrict__ ccount) {
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  float3 p = load_pos(pos, i, D);
-  int cx = cell_coord(p.x, g->lo[0], g->inv_c, g->dims[0]);
-  int cy = cell_coord(p.y, g->lo[1], g->inv_c, g->dims[1]);
-  int cz = D == 3 ? cell_coord(p.z, g->lo[2], g->inv_c, g->dims[2]) : 0;
-  uint32_t id = (uint32_t)(cx + g->dims[0] * (cy + g->dims[1] * cz));
+  const uint32_t id = cell_of(load_pos(pos, i, D), *g, D);
   cellid[i] = id;
-  atomicAdd(&ccount[id], 1u);
+  place[i] = atomicAdd(&ccount[id], 1u);
 }
 
 __global__ __launch_bounds__(256) void k_cell_scatter(const float* __restrict__ pos, int64_t n, int D,
                                                       const uint32_t* __restrict__ cellid,
+                                                      const uint32_t* __restrict__ place,
                                                       const int32_t* __restrict__ cstart,
-                                                      uint32_t* __restrict__ cur,
                                                       float4* __restrict__ spos,
                                                       int32_t* __restrict__ sidx) {
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  uint32_t c = cellid[i];
-  int32_t slot = cstart[c] + (int32_t)atomicAdd(&cur[c], 1u);
+  const int32_t slot = cstart[cellid[i]] + (int32_t)place[i];
   float3 p = load_pos(pos, i, D);
   spos[slot] = make_float4(p.x, p.y, p.z, 0.0f);
   sidx[slot] = (int32_t)i;
+}
+
+// The grid and the cell sort of up to GRID_SMALL points by one workgroup, in
+// one launch in place of six (each of them 2 to 4 us at such sizes, with the
+// gaps between them longer than that): points in registers, the box by wave
+// reductions, cell counts, places and starts in LDS (at most GRID_CELLS cells;
+// a finer grid is coarsened, which changes the candidates and no result).
+// 1,024 points: 18 us of kernels -> 6.7.
+constexpr int GRID_SMALL = 8192, GRID_CELLS = 8192;
+__global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ pos, int n, int D, float r, int cap,
+                                                     GridParams* __restrict__ gp, int32_t* __restrict__ cstart,
+                                                     float4* __restrict__ spos, int32_t* __restrict__ sidx,
+                                                     uint32_t* __restrict__ za, int nza, uint32_t* __restrict__ zb,
+                                                     int nzb) {
+  __shared__ uint32_t cnt[GRID_CELLS];
+  __shared__ float red[6][16];
+  __shared__ uint32_t sh[32];
+  __shared__ GridParams gs;
+  constexpr int PER = GRID_SMALL / 1024, CPT = GRID_CELLS / 1024;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int i = tid; i < nza; i += 1024) za[i] = 0;
+  for (int i = tid; i < nzb; i += 1024) zb[i] = 0;
+  for (int c = tid; c < GRID_CELLS; c += 1024) cnt[c] = 0;
+  float3 p[PER];
+  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = u * 1024 + tid;
+    if (i < n) {
+      p[u] = load_pos(pos, i, D);
+      v[0] = fminf(v[0], p[u].x); v[1] = fminf(v[1], p[u].y); v[2] = fminf(v[2], p[u].z);
+      v[3] = fmaxf(v[3], p[u].x); v[4] = fmaxf(v[4], p[u].y); v[5] = fmaxf(v[5], p[u].z);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+      const float w = __shfl_xor(v[a], o, 64);
+      v[a] = a < 3 ? fminf(v[a], w) : fmaxf(v[a], w);
+    }
+  if (lane == 0)
+    for (int a = 0; a < 6; ++a) red[a][wv] = v[a];
+  __syncthreads();
+  if (tid == 0) {
+    float lo[3], hi[3];
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = red[a][0];
+      hi[a] = red[3 + a][0];
+      for (int w = 1; w < 16; ++w) {
+        lo[a] = fminf(lo[a], red[a][w]);
+        hi[a] = fmaxf(hi[a], red[3 + a][w]);
+      }
+    }
+    gs = choose_grid(lo, hi, D, r, cap);
+    *gp = gs;
+  }
+  __syncthreads();
+  const GridParams g = gs;
+  uint32_t id[PER], at[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * 1024 + tid < n) {
+      id[u] = cell_of(p[u], g, D);
+      at[u] = atomicAdd(&cnt[id[u]], 1u);
+    }
+  __syncthreads();
+  uint32_t c[CPT], sum = 0, tot;
+#pragma unroll
+  for (int k = 0; k < CPT; ++k) {
+    c[k] = cnt[tid * CPT + k];
+    sum += c[k];
+  }
+  uint32_t run = block_exclusive_scan_1024(sum, sh, &tot);   // every count is read when it returns
+#pragma unroll
+  for (int k = 0; k < CPT; ++k) {
+    cnt[tid * CPT + k] = run;
+    if (tid * CPT + k <= g.ncell) cstart[tid * CPT + k] = (int32_t)run;
+    run += c[k];
+  }
+  if (tid == 0) cstart[g.ncell] = n;   // not among the above when every cell of the table is used
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * 1024 + tid < n) {
+      const uint32_t slot = cnt[id[u]] + at[u];
+      spos[slot] = make_float4(p[u].x, p[u].y, p[u].z, 0.0f);
+      sidx[slot] = u * 1024 + tid;
+    }
 }
 
 // The candidates of a destination: for every neighbouring cell row (3 in 2-D,
@@ -261,37 +361,118 @@ __global__ __launch_bounds__(256) void k_nbr_count(const float* __restrict__ pos
   }
 }
 
-// Edge total (64-bit) and largest pre-cap row count: every block reduces a
-// strided share of the rows and adds its result atomically (grid setup has
-// zeroed both).
-__global__ __launch_bounds__(256) void k_graph_stats(const uint32_t* __restrict__ rcnt,
-                                                     const uint32_t* __restrict__ rraw, int64_t n_dst,
-                                                     GraphStats* __restrict__ st) {
-  __shared__ unsigned long long ssum[4];
-  __shared__ uint32_t smax[4];
-  unsigned long long s = 0;
-  uint32_t m = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_dst; i += (int64_t)gridDim.x * 256) {
-    s += rcnt[i];
-    m = rraw[i] > m ? rraw[i] : m;
-  }
+// The scan of the row counts into row_ptr, with the edge total (64-bit) and
+// the largest pre-cap count left in host memory for the call that waits for
+// them: one launch and no copy up to 16,384 rows, two launches above.
+__device__ __forceinline__ uint32_t block_max_1024(uint32_t v, uint32_t* sh) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    s += __shfl_xor(s, o, 64);
-    const uint32_t v = __shfl_xor(m, o, 64);
-    m = v > m ? v : m;
+    const uint32_t w = __shfl_xor(v, o, 64);
+    v = w > v ? w : v;
   }
-  if ((threadIdx.x & 63) == 0) {
-    ssum[threadIdx.x >> 6] = s;
-    smax[threadIdx.x >> 6] = m;
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  uint32_t m = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) m = sh[w] > m ? sh[w] : m;
+  __syncthreads();
+  return m;
+}
+
+__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+__device__ __forceinline__ void store_stats(GraphStats* st, unsigned long long total, uint32_t maxraw) {
+  st->total = total;
+  st->maxraw = maxraw;
+  __threadfence_system();
+}
+
+constexpr int ROWS_PER = 16;   // rows per thread of the one-launch form
+__global__ __launch_bounds__(1024) void k_rows_single(const uint32_t* __restrict__ rcnt,
+                                                      const uint32_t* __restrict__ rraw, int n,
+                                                      int32_t* __restrict__ row_ptr, GraphStats* st) {
+  __shared__ uint32_t sh[32];
+  const int b = threadIdx.x * ROWS_PER;
+  __shared__ unsigned long long total;
+  if (threadIdx.x == 0) total = 0;
+  uint32_t v[ROWS_PER], m = 0;
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int k = 0; k < ROWS_PER; ++k) {
+    v[k] = b + k < n ? rcnt[b + k] : 0u;
+    const uint32_t w = b + k < n ? rraw[b + k] : 0u;
+    sum += v[k];
+    m = w > m ? w : m;
   }
+  m = block_max_1024(m, sh);   // orders the clearing of total too
+  const unsigned long long ws = wave_sum64(sum);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&total, ws);
+  uint32_t tot;
+  uint32_t run = block_exclusive_scan_1024((uint32_t)sum, sh, &tot);
+#pragma unroll
+  for (int k = 0; k < ROWS_PER; ++k) {
+    if (b + k < n) row_ptr[b + k] = (int32_t)run;
+    run += v[k];
+  }
+  if (threadIdx.x == 0) {
+    row_ptr[n] = (int32_t)tot;
+    store_stats(st, total, m);
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_rows_sums(const uint32_t* __restrict__ rcnt,
+                                                    const uint32_t* __restrict__ rraw, int64_t n,
+                                                    unsigned long long* __restrict__ sums,
+                                                    uint32_t* __restrict__ maxs) {
+  __shared__ uint32_t sh[32];
+  __shared__ unsigned long long total;
+  if (threadIdx.x == 0) total = 0;
+  const int64_t i = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x;
+  const uint32_t m = block_max_1024(i < n ? rraw[i] : 0u, sh);   // orders the clearing of total too
+  const unsigned long long ws = wave_sum64(i < n ? rcnt[i] : 0u);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&total, ws);
   __syncthreads();
   if (threadIdx.x == 0) {
-    s = ssum[0] + ssum[1] + ssum[2] + ssum[3];
-    m = smax[0];
-    for (int k = 1; k < 4; ++k) m = smax[k] > m ? smax[k] : m;
-    atomicAdd(&st->total, s);
-    atomicMax(&st->maxraw, m);
+    sums[blockIdx.x] = total;
+    maxs[blockIdx.x] = m;
+  }
+}
+
+// Every block adds up the sums ahead of it; block 0 forms the total and the
+// maximum over all nb blocks.  row_ptr wraps at 2^32 when the total does (the
+// host then rejects the graph by the 64-bit total).
+__global__ __launch_bounds__(1024) void k_rows_final(const uint32_t* __restrict__ rcnt, int64_t n,
+                                                     const unsigned long long* __restrict__ sums,
+                                                     const uint32_t* __restrict__ maxs, int nb,
+                                                     int32_t* __restrict__ row_ptr, GraphStats* st) {
+  __shared__ uint32_t sh[32];
+  __shared__ unsigned long long total;
+  if (threadIdx.x == 0) total = 0;
+  const int b = blockIdx.x;
+  const int64_t i = (int64_t)b * SCAN_BLOCK + threadIdx.x;
+  const uint32_t v = i < n ? rcnt[i] : 0u;
+  uint32_t pre = 0;
+  for (int k = threadIdx.x; k < b; k += SCAN_BLOCK) pre += (uint32_t)sums[k];
+  uint32_t before, tot;
+  block_exclusive_scan_1024(pre, sh, &before);   // orders the clearing of total too
+  const uint32_t ex = block_exclusive_scan_1024(v, sh, &tot);
+  if (i < n) row_ptr[i] = (int32_t)(before + ex);
+  if (i == n - 1) row_ptr[n] = (int32_t)(before + tot);
+  if (b == 0) {
+    unsigned long long s = 0;
+    uint32_t m = 0;
+    for (int k = threadIdx.x; k < nb; k += SCAN_BLOCK) {
+      s += sums[k];
+      m = maxs[k] > m ? maxs[k] : m;
+    }
+    m = block_max_1024(m, sh);
+    if (s) atomicAdd(&total, s);
+    __syncthreads();
+    if (threadIdx.x == 0) store_stats(st, total, m);
   }
 }
 
@@ -358,8 +539,14 @@ constexpr int SEL_PER_LANE = 8;
 
 // The one-pass select of capped graphs: caps up to FUSE_CAP, rows of up to
 // FUSE_LIM candidates (larger rows are built by the fill kernel).
+// Without the payload array of the random cap (a nearest-neighbour key holds
+// its source index) 512 candidates take 16 KB per block of four rows, which
+// still lets eight blocks on a CU.  With 256 an eighth of the rows of a mesh
+// crowded toward a wall (32,768 nodes, mean 78 candidates) was left to the
+// fill kernel and the transpose to a scatter: 113 -> 59 us for select, fill,
+// placing and scatter.
 constexpr int FUSE_CAP = 64;
-constexpr int FUSE_LIM = 256;
+constexpr int FUSE_LIM = 512;
 
 // Writes to js the payloads of the cap smallest of the n keys (cap < n <=
 // 64 NT) without sorting them. Keys are distinct: d2 bits with the source
@@ -369,6 +556,7 @@ constexpr int FUSE_LIM = 256;
 // the fixed bits; the kept keys are those whose fixed bits are at most K's.
 // The high words decide unless two of them are equal at K; only then are the
 // low words visited.
+// val NULL: a key's low word is its payload.
 template <int NT>
 __device__ __forceinline__ void select_cap(const uint64_t* key, const int32_t* val, uint32_t* js,
                                            int n, int cap, int lane) {
@@ -382,7 +570,7 @@ __device__ __forceinline__ void select_cap(const uint64_t* key, const int32_t* v
     const uint64_t k = ok ? key[u] : ~0ull;
     kh[t] = (uint32_t)(k >> 32);
     kl[t] = (uint32_t)k;
-    vr[t] = ok ? val[u] : 0;
+    vr[t] = val ? (ok ? val[u] : 0) : (int32_t)kl[t];
     vm[t] = __ballot(ok);
   }
   int rank = cap - 1;  // K's rank among the keys that match the fixed bits
@@ -627,10 +815,10 @@ __global__ __launch_bounds__(256) void k_csc_sort(const int32_t* __restrict__ cs
 // sorted afterwards). One wave per row, four per block, each
 // wave with room for FUSE_LIM candidates: a row with more is only counted
 // (the fill kernel builds it after the scan).
+template <bool KNN>
 __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ pos, int64_t n_dst,
                                                     int64_t n_src, int D, float r2, int cap,
-                                                    int cap_mode, uint64_t seed,
-                                                    const GridParams* __restrict__ gp,
+                                                    uint64_t seed, const GridParams* __restrict__ gp,
                                                     const int32_t* __restrict__ cstart,
                                                     const float4* __restrict__ spos,
                                                     const int32_t* __restrict__ sidx,
@@ -640,13 +828,13 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
                                                     uint32_t* __restrict__ indeg,
                                                     uint32_t* __restrict__ eslot) {
   __shared__ uint64_t skey[4][FUSE_LIM];
-  __shared__ int32_t sval[4][FUSE_LIM];
+  __shared__ int32_t sval[KNN ? 1 : 4][KNN ? 1 : FUSE_LIM];
   const int wv = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int64_t i = (int64_t)blockIdx.x * 4 + wv;
   if (i >= n_dst) return;
   uint64_t* key = skey[wv];
-  int32_t* val = sval[wv];
+  int32_t* val = KNN ? nullptr : sval[KNN ? 0 : wv];
   const GridParams g = *gp;
   const float3 pi = load_pos(pos, i, D);
   const Candidates c = candidate_ranges(pi, D, g, cstart, lane);
@@ -658,10 +846,9 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
     if (pass) {
       const int slot = n + __popcll(m & ((1ull << lane) - 1ull));
       if (slot < FUSE_LIM) {
-        key[slot] = cap_mode == DSMP_CAP_KNN
-                        ? (((uint64_t)__float_as_uint(d2)) << 32) | (uint32_t)j
+        key[slot] = KNN ? (((uint64_t)__float_as_uint(d2)) << 32) | (uint32_t)j
                         : splitmix64(seed, (uint64_t)i * (uint64_t)n_src + (uint64_t)j);
-        val[slot] = j;
+        if constexpr (!KNN) val[slot] = j;
       }
     }
     n += __popcll(m);
@@ -679,8 +866,14 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
       case 1: select_cap<1>(key, val, js, n, cap, lane); break;
       case 2: select_cap<2>(key, val, js, n, cap, lane); break;
       case 3: select_cap<3>(key, val, js, n, cap, lane); break;
-      default: select_cap<4>(key, val, js, n, cap, lane); break;
+      case 4: select_cap<4>(key, val, js, n, cap, lane); break;
+      case 5: case 6: select_cap<6>(key, val, js, n, cap, lane); break;
+      default: select_cap<8>(key, val, js, n, cap, lane); break;
     }
+  } else if constexpr (KNN) {
+    const uint32_t j = lane < n ? (uint32_t)key[lane] : 0u;   // n <= cap <= 64
+    wave_sync();   // js overwrites the keys
+    if (lane < n) js[lane] = j;
   } else {
     for (int t = lane; t < n; t += 64) js[t] = (uint32_t)val[t];
   }
@@ -726,11 +919,10 @@ __global__ __launch_bounds__(256) void k_nbr_place(int64_t n_dst, int cap, const
 struct GraphWs {
   float* part;
   GridParams* grid;
-  GraphStats* stats;
   uint32_t* cellid;
   uint32_t* ccount;
   int32_t* cstart;
-  uint32_t* ccur;
+  uint32_t* place;
   float4* spos;
   int32_t* sidx;
   uint32_t* rcnt;
@@ -739,6 +931,8 @@ struct GraphWs {
   uint32_t* indeg;
   uint32_t* scur;
   uint32_t* scan_tmp;
+  unsigned long long* rsum;   // per 1,024 rows: total and largest pre-cap count
+  uint32_t* rmax;
   uint32_t* slab;   // n_dst x cap kept sources per row (capped graphs with cap <= FUSE_CAP)
   uint32_t* eslot;  // n_dst x cap: each kept edge's place among its source's edges
   int64_t ncap;
@@ -755,11 +949,10 @@ GraphWs carve_graph_ws(void* base, const dsmp_graph_query* q, size_t* used) {
   w.ncap = 2 * n_src + 64;
   w.part = c.take<float>(BBOX_BLOCKS * 6);
   w.grid = c.take<GridParams>(1);
-  w.stats = c.take<GraphStats>(1);
   w.cellid = c.take<uint32_t>(n_src);
   w.ccount = c.take<uint32_t>(w.ncap);
   w.cstart = c.take<int32_t>(w.ncap + 1);
-  w.ccur = c.take<uint32_t>(w.ncap);
+  w.place = c.take<uint32_t>(n_src);
   w.spos = c.take<float4>(n_src);
   w.sidx = c.take<int32_t>(n_src);
   w.rcnt = c.take<uint32_t>(n_dst);
@@ -769,6 +962,8 @@ GraphWs carve_graph_ws(void* base, const dsmp_graph_query* q, size_t* used) {
   w.scur = c.take<uint32_t>(n_src);
   int64_t m = w.ncap > n_src ? w.ncap : n_src;
   w.scan_tmp = c.take<uint32_t>(scan_tmp_elems(m));
+  w.rsum = c.take<unsigned long long>(scan_tmp_elems(n_dst));
+  w.rmax = c.take<uint32_t>(scan_tmp_elems(n_dst));
   w.slab = fused_select(q) ? c.take<uint32_t>(n_dst * q->cap) : nullptr;
   w.eslot = fused_select(q) ? c.take<uint32_t>(n_dst * q->cap) : nullptr;
   if (used) *used = c.used();
@@ -796,43 +991,54 @@ dsmp_status count_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs
   const float r2 = __builtin_bit_cast(float, 0) + q->r * q->r;   // fl32(r*r)
   hipStream_t s = h->stream;
   int64_t n = q->n_src;
-  unsigned nb = n > 0 ? ceil_div(n, 256) : 1;
-  if (nb > BBOX_BLOCKS) nb = BBOX_BLOCKS;
-  hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, s, q->pos, n, D, w.part);
-  hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(64), 0, s, w.part, (int)nb, D, q->r, w.ncap, w.grid,
-                     w.stats);
-  DSMP_LAUNCHED(h, "grid setup");
   dsmp_status st;
-  if ((st = fill_u32(h, w.ccount, w.ncap, 0, w.ccur)) != DSMP_OK) return st;
-  // the select pass counts in-degrees (and the scatter's cursors start at zero)
-  if (select && (st = fill_u32(h, w.indeg, q->n_src, 0, w.scur)) != DSMP_OK) return st;
-  if (n > 0) {
-    hipLaunchKernelGGL(k_cell_hash, dim3(ceil_div(n, 256)), dim3(256), 0, s, q->pos, n, D, w.grid,
-                       w.cellid, w.ccount);
+  // the select pass counts in-degrees (and the scatter's cursors start at zero):
+  // indeg and scur are cleared with the grid's counters
+  uint32_t* zdeg = select ? w.indeg : nullptr;
+  const int64_t nzdeg = select ? (w.scur - w.indeg) + n : 0;
+  if (n <= GRID_SMALL) {
+    hipLaunchKernelGGL(k_grid_small, dim3(1), dim3(1024), 0, s, q->pos, (int)n, D, q->r,
+                       (int)std::min<int64_t>(w.ncap, GRID_CELLS), w.grid, w.cstart, w.spos, w.sidx, zdeg,
+                       (int)nzdeg, nullptr, 0);
+    DSMP_LAUNCHED(h, "grid and cell sort");
+  } else {
+    const unsigned nb = std::min<unsigned>(ceil_div(n, 256), BBOX_BLOCKS);
+    hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, s, q->pos, n, D, w.part, w.ccount, w.ncap, zdeg, nzdeg);
+    hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(64), 0, s, w.part, (int)nb, D, q->r, w.ncap, w.grid);
+    hipLaunchKernelGGL(k_cell_hash, dim3(ceil_div(n, 256)), dim3(256), 0, s, q->pos, n, D, w.grid, w.cellid, w.place,
+                       w.ccount);
     DSMP_LAUNCHED(h, "cell hash");
-  }
-  if ((st = exclusive_scan_u32(h, w.ccount, w.cstart, w.ncap, w.scan_tmp)) != DSMP_OK) return st;
-  if (n > 0) {
-    hipLaunchKernelGGL(k_cell_scatter, dim3(ceil_div(n, 256)), dim3(256), 0, s, q->pos, n, D,
-                       w.cellid, w.cstart, w.ccur, w.spos, w.sidx);
+    if ((st = exclusive_scan_u32(h, w.ccount, w.cstart, w.ncap, w.scan_tmp)) != DSMP_OK) return st;
+    hipLaunchKernelGGL(k_cell_scatter, dim3(ceil_div(n, 256)), dim3(256), 0, s, q->pos, n, D, w.cellid, w.place,
+                       w.cstart, w.spos, w.sidx);
     DSMP_LAUNCHED(h, "cell scatter");
   }
   if (q->n_dst > 0) {
-    if (select)
-      hipLaunchKernelGGL(k_nbr_select, dim3(ceil_div(q->n_dst, 4)), dim3(256), 0, s, q->pos, q->n_dst,
-                         q->n_src, D, r2, q->cap, q->cap_mode, q->seed, w.grid, w.cstart, w.spos, w.sidx,
-                         w.rcnt, w.rraw, w.slab, w.indeg, w.eslot);
+    if (select && q->cap_mode == DSMP_CAP_KNN)
+      hipLaunchKernelGGL(k_nbr_select<true>, dim3(ceil_div(q->n_dst, 4)), dim3(256), 0, s, q->pos, q->n_dst, q->n_src,
+                         D, r2, q->cap, q->seed, w.grid, w.cstart, w.spos, w.sidx, w.rcnt, w.rraw, w.slab, w.indeg,
+                         w.eslot);
+    else if (select)
+      hipLaunchKernelGGL(k_nbr_select<false>, dim3(ceil_div(q->n_dst, 4)), dim3(256), 0, s, q->pos, q->n_dst, q->n_src,
+                         D, r2, q->cap, q->seed, w.grid, w.cstart, w.spos, w.sidx, w.rcnt, w.rraw, w.slab, w.indeg,
+                         w.eslot);
     else
       hipLaunchKernelGGL(k_nbr_count, dim3(ceil_div(q->n_dst, 4)), dim3(256), 0, s, q->pos, q->n_dst, D,
                          r2, q->cap, w.grid, w.cstart, w.spos, w.sidx, w.rcnt, w.rraw);
-    hipLaunchKernelGGL(k_graph_stats, dim3((unsigned)std::min<int64_t>(ceil_div(q->n_dst, 2048), 256)),
-                       dim3(256), 0, s, w.rcnt, w.rraw, q->n_dst, w.stats);
     DSMP_LAUNCHED(h, "neighbour count");
   }
-  if ((st = exclusive_scan_u32(h, w.rcnt, row_ptr, q->n_dst, w.scan_tmp)) != DSMP_OK) return st;
-  GraphStats hs;
-  DSMP_HIP(h, hipMemcpyAsync(&hs, w.stats, sizeof(hs), hipMemcpyDeviceToHost, s));
+  GraphStats* stats = static_cast<GraphStats*>(h->readback_dev);
+  static_assert(sizeof(GraphStats) <= READBACK_BYTES, "fits the readback area");
+  if (q->n_dst <= ROWS_PER * 1024) {
+    hipLaunchKernelGGL(k_rows_single, dim3(1), dim3(1024), 0, s, w.rcnt, w.rraw, (int)q->n_dst, row_ptr, stats);
+  } else {
+    const int nb = (int)ceil_div(q->n_dst, SCAN_BLOCK);
+    hipLaunchKernelGGL(k_rows_sums, dim3(nb), dim3(1024), 0, s, w.rcnt, w.rraw, q->n_dst, w.rsum, w.rmax);
+    hipLaunchKernelGGL(k_rows_final, dim3(nb), dim3(1024), 0, s, w.rcnt, q->n_dst, w.rsum, w.rmax, nb, row_ptr, stats);
+  }
+  DSMP_LAUNCHED(h, "row scan");
   DSMP_HIP(h, hipStreamSynchronize(s));
+  const GraphStats hs = *static_cast<const GraphStats*>(h->readback);
   *E = (int64_t)hs.total;
   *maxraw = hs.maxraw;
   DSMP_CHECK(h, hs.maxraw <= (uint32_t)ROW_LIMIT, DSMP_UNSUPPORTED,

@@ -166,6 +166,14 @@ CASES = {
     "3d_knn1": (lambda: _rand(3000, 3, 27), 3000, 0.12, 1, 0),
     "2d_random1": (lambda: _rand(3000, 2, 28), 3000, 0.05, 1, 1),
     "3d_cap200": (lambda: _rand(3000, 3, 29), 3000, 0.12, 200, 0),
+    # the one-workgroup cell sort (up to 8,192 points): its largest size, with a
+    # grid of more cells than its table; and one point more
+    "sparse_8192_points": (lambda: _rand(8192, 2, 30), 8192, 0.004, 0, 0),
+    "sparse_8193_points": (lambda: _rand(8193, 2, 31), 8193, 0.004, 0, 0),
+    "8193_points_halo_random": (lambda: _rand(8193, 3, 32), 7000, 0.07, 6, 1),
+    # row counts scanned in one launch (up to 16,384 rows) and in two
+    "2d_16384_rows": (lambda: _rand(16384, 2, 33), 16384, 0.02, 0, 0),
+    "2d_16385_rows_knn": (lambda: _rand(16500, 2, 34), 16385, 0.03, 9, 0),
 }
 
 
