@@ -446,8 +446,8 @@ bool use_aggregate(const dsmp_handle* h, const dsmp_layer_desc& d, int64_t n_dst
 int64_t agg_ktot(const dsmp_layer_desc& d);
 int agg_gemm_slices(int64_t n_rows, const dsmp_layer_desc& d);
 int agg_dw3_slices(int64_t n_rows);
-dsmp_status launch_outer_sum(dsmp_handle* h, const dsmp_layer_desc& d, int64_t n_seg, const int32_t* seg_ptr,
-                             const int32_t* pos_eid, const int32_t* row_of, const unsigned char* zE,
+dsmp_status launch_outer_sum(dsmp_handle* h, const dsmp_layer_desc& d, int64_t n_seg, int64_t n_edges,
+                             const int32_t* seg_ptr, const int32_t* pos_eid, const int32_t* row_of, const unsigned char* zE,
                              const unsigned char* u, unsigned char* out);
 dsmp_status launch_w3_gemm(dsmp_handle* h, const dsmp_layer_desc& d, int64_t n_rows, const unsigned char* A,
                            const unsigned char* BT, int nsl, float* part);

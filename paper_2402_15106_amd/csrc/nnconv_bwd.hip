@@ -3088,7 +3088,7 @@ extern "C" dsmp_status dsmp_nnconv_backward(dsmp_handle* h, const dsmp_layer_des
     // per-source sums T_j = sum_e [z_e; 1] (x) g_e, then one GEMM with W3~
     {
       ProfScope prof(h, DSMP_K_OUTER_DH);
-      st = launch_outer_sum(h, d, n_src, g->csc_ptr, g->csc_eid, g->dst, sv + sl.zE, w.gT, w.ot);
+      st = launch_outer_sum(h, d, n_src, E, g->csc_ptr, g->csc_eid, g->dst, sv + sl.zE, w.gT, w.ot);
     }
     if (st != DSMP_OK) return st;
     {

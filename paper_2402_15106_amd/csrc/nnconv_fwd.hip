@@ -1175,7 +1175,7 @@ extern "C" dsmp_status dsmp_nnconv_forward(dsmp_handle* h, const dsmp_layer_desc
     if ((st = launch_edge_contract(h, d, MODE_MLP, ea)) != DSMP_OK) return st;
     {
       ProfScope prof(h, DSMP_K_OUTER_FWD);
-      st = launch_outer_sum(h, d, g->n_dst, g->row_ptr, nullptr, g->col, sv + sl.zE,
+      st = launch_outer_sum(h, d, g->n_dst, g->n_edges, g->row_ptr, nullptr, g->col, sv + sl.zE,
                             static_cast<const unsigned char*>(h_in), sv + sl.os);
     }
     if (st != DSMP_OK) return st;
