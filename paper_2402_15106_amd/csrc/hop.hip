@@ -254,29 +254,35 @@ typedef float f32x16m __attribute__((ext_vector_type(16)));
 
 // C += sum over k < K of A(r, k) B(k, c) for the 32x32 block of rows
 // [0, 32) and columns [c0, c0 + 32): A row-major with pitch pa, B given as
-// Bt row-major [c][k] (pitch pb, rows >= nc read as zero), two k per step.
-__device__ __forceinline__ f32x16m mchain_rows(f32x16m C, int K, const float* A, int pa, const float* Bt, int pb,
-                                              int c0, int nc) {
+// Bt row-major [c][k] (COLS false; rows >= nc read as zero) or as [k][c]
+// (COLS true; columns >= nc read as zero), pitch pb, two k per step.  The
+// chain of products is serial; whole groups of eight steps read their
+// operands ahead of it, unconditionally (a read past nc is of the last column
+// and replaced by zero).
+template <bool COLS>
+__device__ __forceinline__ f32x16m mchain(f32x16m C, int K, const float* A, int pa, const float* B, int pb, int c0,
+                                         int nc) {
   const int l = threadIdx.x & 63, r = l & 31, h = l >> 5;
   const bool cv = c0 + r < nc;
-  for (int kk = 0; kk < K; kk += 2) {
-    const int k = kk + h;
-    const float av = k < K ? A[r * pa + k] : 0.0f;
-    const float bv = k < K && cv ? Bt[(c0 + r) * pb + k] : 0.0f;
-    C = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, C, 0, 0, 0);
+  const int c = cv ? c0 + r : nc - 1;
+  const int bk = COLS ? pb : 1;
+  const float* ar = A + r * pa;
+  const float* br = B + (COLS ? c : c * pb);
+  int kk = 0;
+  for (; kk + 16 <= K; kk += 16) {
+    float av[8], bv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      av[u] = ar[kk + 2 * u + h];
+      bv[u] = br[(kk + 2 * u + h) * bk];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) C = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], cv ? bv[u] : 0.0f, C, 0, 0, 0);
   }
-  return C;
-}
-
-// The same with B row-major [k][c] (pitch pb, columns >= nc read as zero).
-__device__ __forceinline__ f32x16m mchain_cols(f32x16m C, int K, const float* A, int pa, const float* B, int pb,
-                                              int c0, int nc) {
-  const int l = threadIdx.x & 63, r = l & 31, h = l >> 5;
-  const bool cv = c0 + r < nc;
-  for (int kk = 0; kk < K; kk += 2) {
+  for (; kk < K; kk += 2) {
     const int k = kk + h;
-    const float av = k < K ? A[r * pa + k] : 0.0f;
-    const float bv = k < K && cv ? B[k * pb + c0 + r] : 0.0f;
+    const float av = k < K ? ar[k] : 0.0f;
+    const float bv = k < K && cv ? br[k * bk] : 0.0f;
     C = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, C, 0, 0, 0);
   }
   return C;
@@ -293,7 +299,7 @@ __device__ __forceinline__ void mdense(int cnt, int K, int O, const float* in_s,
     f32x16m C;
 #pragma unroll
     for (int i = 0; i < 16; ++i) C[i] = bc;
-    C = mchain_rows(C, K, in_s, K + 1, W_s, K + 1, ob * 32, O);
+    C = mchain<false>(C, K, in_s, K + 1, W_s, K + 1, ob * 32, O);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i / 4) + 4 * h + (i % 4);
@@ -318,7 +324,7 @@ __device__ __forceinline__ void mdense_back(int cnt, int K, int O, const float* 
   for (int kb = wv; kb * 32 < K; kb += 4) {
     const int c = kb * 32 + r;
     f32x16m C = f32x16m{};
-    C = mchain_cols(C, O, g_s, O + 1, W_s, K + 1, kb * 32, K);
+    C = mchain<true>(C, O, g_s, O + 1, W_s, K + 1, kb * 32, K);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i / 4) + 4 * h + (i % 4);
@@ -339,34 +345,80 @@ __device__ __forceinline__ void mdense_back(int cnt, int K, int O, const float* 
 // read as g[r][o]), its contraction index the tile's rows.
 __device__ __forceinline__ void mouter(int K, int O, const float* g_s, const float* in_s, float* part) {
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, r = l & 31, h = l >> 5;
-  const int nob = (O + 31) / 32, nkb = (K + 1 + 31) / 32;
+  // whole 32-column blocks of k leave the column of ones a block of its own: its
+  // sums (the bias gradient) are added up by threads of their own instead, in
+  // the same order
+  const bool ones = K % 32 != 0;
+  const int nob = (O + 31) / 32, nkb = (K + (ones ? 1 : 0) + 31) / 32;
   for (int t = wv; t < nob * nkb; t += 4) {
     const int ob = t / nkb, kb = t % nkb;
     const int o = ob * 32 + r, c = kb * 32 + r;
+    const float* ga = g_s + (o < O ? o : O - 1);
+    const float* xa = in_s + (c < K ? c : K - 1);
+    const float one = c == K ? 1.0f : 0.0f;
     f32x16m C = f32x16m{};
+#pragma unroll
     for (int kk = 0; kk < FR; kk += 2) {
       const int rr = kk + h;
-      const float av = o < O ? g_s[rr * (O + 1) + o] : 0.0f;
-      const float bv = c < K ? in_s[rr * (K + 1) + c] : (c == K ? 1.0f : 0.0f);
-      C = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, C, 0, 0, 0);
+      const float av = ga[rr * (O + 1)], bv = xa[rr * (K + 1)];
+      C = __builtin_amdgcn_mfma_f32_32x32x2f32(o < O ? av : 0.0f, c < K ? bv : one, C, 0, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int oo = ob * 32 + 8 * (i / 4) + 4 * h + (i % 4);
-      if (oo < O && c <= K) part[oo * (K + 1) + c] = C[i];
+      if (oo < O && (c < K || (ones && c == K))) part[oo * (K + 1) + c] = C[i];
     }
   }
+  if (!ones)
+    for (int o = threadIdx.x; o < O; o += 256) {
+      float v = 0.0f;
+#pragma unroll
+      for (int rr = 0; rr < FR; ++rr) v += g_s[rr * (O + 1) + o];
+      part[o * (K + 1) + K] = v;
+    }
 }
 
 // A [rows][w] row-major global matrix (w <= 256) to LDS with pitch w + 1,
-// rows past `valid` as zeros: each thread keeps one column and steps over
-// the rows 256 / w at a time (one division per thread, none per element).
+// rows past `valid` as zeros.  Rows of whole 64-float pieces go by direct copies
+// (each wave one piece per instruction), all of a pass's matrices in flight at
+// once: complete after stage_done().  Other widths: each thread keeps one
+// column and steps over the rows 256 / w at a time (one division per thread,
+// none per element), eight loads ahead of their writes.  A perceptron of
+// 3 -> 64 -> 64 -> 64 on 8,192 rows spent most of its time on one load and wait
+// per element here: forward 29 -> 15 us, backward 47 -> 30.
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) void gbl_void;
 __device__ __forceinline__ void stage_mat(float* dst, const float* src, int rows, int w, int valid) {
+  if (w % 64 == 0) {
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int r = wv; r < rows; r += 4)
+      for (int c = 0; c < w; c += 64) {
+        float* d = dst + r * (w + 1) + c;
+        if (r < valid)
+          __builtin_amdgcn_global_load_lds((gbl_void*)(src + (int64_t)r * w + c + lane), (lds_void*)d, 4, 0, 0);
+        else
+          d[lane] = 0.0f;
+      }
+    return;
+  }
   const int per = 256 / w, t = threadIdx.x, r0 = t / w, c = t - r0 * w;
-  if (r0 >= per) return;
-  for (int rr = r0; rr < rows; rr += per)
-    dst[rr * (w + 1) + c] = rr < valid ? src[(int64_t)rr * w + c] : 0.0f;
+  if (r0 >= per || valid <= 0) return;
+  for (int rr = r0; rr < rows; rr += 8 * per) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = rr + u * per;
+      v[u] = src[(int64_t)(r < valid ? r : valid - 1) * w + c];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = rr + u * per;
+      if (r < rows) dst[r * (w + 1) + c] = r < valid ? v[u] : 0.0f;
+    }
+  }
 }
+// Waits for this wave's copies (before the barrier that publishes them).
+__device__ __forceinline__ void stage_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // Rows [0, cnt) of a [*][w] global matrix to LDS with pitch w + 1, zeros past cnt.
 __device__ __forceinline__ void stage_rows(float* dst, const float* src, int cnt, int w) {
@@ -403,8 +455,9 @@ __global__ __launch_bounds__(256) void k_mlp_fwd_m(MlpArgs a) {
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t r0 = tile * FR;
     const int cnt = (int)std::min<int64_t>(FR, a.n - r0);
-    __syncthreads();   // weights staged / the previous tile consumed
+    if (tile != (int64_t)blockIdx.x) __syncthreads();   // the previous tile is consumed
     stage_rows(sm + m.x, a.x + r0 * a.din, cnt, a.din);
+    stage_done();      // the rows, and before the first tile the weights
     __syncthreads();
     mdense(cnt, a.din, a.dh, sm + m.x, sm + m.w1, a.b1, 1, sm + m.s1, a.h1 + r0 * a.dh, nullptr);
     __syncthreads();
@@ -427,6 +480,7 @@ __global__ __launch_bounds__(256) void k_mlp_bwd_m(MlpArgs a) {
   stage_rows(sm + m.g3, a.gy + r0 * a.dout, cnt, a.dout);
   stage_rows(sm + m.s1, a.h1 + r0 * a.dh, cnt, a.dh);
   stage_rows(sm + m.s2, a.h2 + r0 * a.dh, cnt, a.dh);
+  stage_done();
   __syncthreads();
   mdense_back(cnt, a.dh, a.dout, sm + m.g3, sm + m.w3, sm + m.s2, sm + m.g2, nullptr, 0);
   __syncthreads();

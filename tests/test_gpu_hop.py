@@ -67,6 +67,13 @@ def test_mlp_forward_backward(env, n, d_in, d_hid, d_out):
         assert rel_err(gx.cpu().numpy(), 2 * rgx) <= TOL["f32"]
 
 
+# a partial and a full last tile at widths that are copied to LDS in whole rows,
+# and at widths that are not (a column of ones of its own, odd inputs)
+@pytest.mark.parametrize("n,d_in,d_hid,d_out", [(33, 64, 64, 64), (31, 128, 32, 5), (70, 33, 96, 40), (64, 16, 128, 1)])
+def test_mlp_staged_widths(env, n, d_in, d_hid, d_out):
+    test_mlp_forward_backward(env, n, d_in, d_hid, d_out)
+
+
 @pytest.mark.parametrize("n,c,frac", [(3000, 3, 0.7), (300, 4, 1.0), (17, 2, 0.0), (0, 3, 1.0)])
 def test_masked_mse(env, n, c, frac):
     dm, lib, torch = env
