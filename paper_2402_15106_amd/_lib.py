@@ -327,10 +327,23 @@ class Dsmp:
 
     def dsmp_radius_graph_build(self, pos, n_dst, r, cap=0, cap_mode=CAP_KNN, seed=0,
                                 capacity: Optional[int] = None, out: Optional[Graph] = None) -> Graph:
+        if out is None and capacity is None:
+            # room for 64 edges per destination (the cap, if lower) saves a counting
+            # call, which does most of the build's work; a graph with more says
+            # how many and is built again
+            guess = n_dst * min(cap, 64) if cap > 0 else n_dst * 64
+            try:
+                g = self.dsmp_radius_graph_build(pos, n_dst, r, cap, cap_mode, seed, capacity=guess)
+            except DsmpError as e:
+                if e.status != CAPACITY:
+                    raise
+                E = self.dsmp_radius_graph_count(pos, n_dst, r, cap, cap_mode, seed)
+                return self.dsmp_radius_graph_build(pos, n_dst, r, cap, cap_mode, seed, capacity=E)
+            n = max(g.n_edges, 1)
+            g.col, g.dst, g.csc_eid = g.col[:n], g.dst[:n], g.csc_eid[:n]
+            return g
         q, pos = self._query(pos, n_dst, r, cap, cap_mode, seed)
         if out is None:
-            if capacity is None:
-                capacity = self.dsmp_radius_graph_count(pos, n_dst, r, cap, cap_mode, seed)
             i32 = dict(dtype=torch.int32, device=self.device)
             out = Graph(n_dst, pos.shape[0], 0, torch.empty(n_dst + 1, **i32),
                         torch.empty(max(capacity, 1), **i32), torch.empty(max(capacity, 1), **i32),

@@ -185,6 +185,21 @@ def test_graph_bit_exact(env, name):
     _check_graph(lib, torch, mk(), n_dst, r, cap, mode, seed=123)
 
 
+@pytest.mark.parametrize("r,cap", [(0.05, 0), (0.2, 0), (0.2, 80), (0.05, 5), (1e-6, 0)])
+def test_graph_built_without_a_capacity(env, r, cap):
+    """Without a capacity the arrays come with the graph's own size, also where
+    it has more than 64 edges per destination."""
+    dm, lib, torch = env
+    announce("graph without capacity", r, cap)
+    pos = _rand(1000, 2, 40)
+    g = lib.dsmp_radius_graph_build(torch.from_numpy(pos).cuda(), 1000, r, cap)
+    rp, col = org.radius_graph(pos, 1000, r, cap)
+    E = int(rp[-1])
+    assert g.n_edges == E and g.col.numel() == g.dst.numel() == g.csc_eid.numel() == max(E, 1)
+    assert np.array_equal(g.row_ptr.cpu().numpy(), rp) and np.array_equal(g.col[:E].cpu().numpy(), col)
+    assert np.array_equal(g.csc_eid[:E].cpu().numpy(), org.transpose(rp, col, 1000)[1])
+
+
 @pytest.mark.parametrize("cap", [0, 10])
 def test_graph_capacity_error_reports_E(env, cap):
     dm, lib, torch = env
