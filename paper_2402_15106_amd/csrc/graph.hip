@@ -257,10 +257,10 @@ __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ p
 // 9 in 3-D) the three cells along x are one contiguous range of the
 // cell-sorted arrays. Lane k < 9 loads the bounds of range k, so that all of
 // them are in flight at once; the ranges are then numbered as one flat list of
-// `total` candidates (wave-uniform starts a[k] and flat offsets off[k]).
+// `total` candidates: lane k keeps the flat offset off of range k's first
+// candidate and the difference base between its place in the arrays and that.
 struct Candidates {
-  int a[9];
-  int off[9];
+  int base, off;   // of range `lane` (lanes past the ranges: off = total)
   int total;
 };
 
@@ -289,23 +289,10 @@ __device__ __forceinline__ Candidates candidate_ranges(float3 p, int D, const Gr
     if (lane >= o) inc += v;
   }
   Candidates c;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    c.a[k] = __builtin_amdgcn_readlane(a, k);
-    c.off[k] = __builtin_amdgcn_readlane(inc - len, k);
-  }
+  c.off = inc - len;
+  c.base = a - c.off;
   c.total = __builtin_amdgcn_readlane(inc, 15);
   return c;
-}
-
-// Position in the cell-sorted arrays of flat candidate t (0 <= t < total).
-// Offsets never decrease, so the last range whose offset is at most t holds it.
-__device__ __forceinline__ int candidate_at(const Candidates& c, int t) {
-  int s = c.a[0] + t;
-#pragma unroll
-  for (int k = 1; k < 9; ++k)
-    if (t >= c.off[k]) s = c.a[k] + (t - c.off[k]);
-  return s;
 }
 
 // Candidates are read CAND_BATCHES x 64 at a time, all loads issued before the
@@ -314,23 +301,38 @@ constexpr int CAND_BATCHES = 4;
 
 // Calls f(t, q, j) for every flat candidate t of a destination, with its
 // position and source index; lanes past the end get t >= total. Every lane of
-// the wave calls f the same number of times.
+// the wave calls f the same number of times.  A batch's candidates lie in a
+// few consecutive ranges, found by a scalar walk (rk: the last range that
+// begins at or before the batch), so a candidate costs a compare and a select
+// per range its batch touches, not per range there is; batches past the end
+// are left out.
 template <typename F>
 __device__ __forceinline__ void for_each_candidate(const Candidates& c, int lane,
                                                    const float4* __restrict__ spos,
                                                    const int32_t* __restrict__ sidx, F f) {
+  int rk = 0;
   for (int t0 = 0; t0 < c.total; t0 += 64 * CAND_BATCHES) {
     float4 q[CAND_BATCHES];
     int32_t j[CAND_BATCHES];
 #pragma unroll
     for (int u = 0; u < CAND_BATCHES; ++u) {
-      const int t = t0 + 64 * u + lane;
-      const int sidx_pos = candidate_at(c, t < c.total ? t : c.total - 1);
-      q[u] = spos[sidx_pos];
-      j[u] = sidx[sidx_pos];
+      const int tb = t0 + 64 * u;
+      if (tb < c.total) {
+        const int t = tb + lane, tc = t < c.total ? t : c.total - 1;
+        while (rk < 8 && __builtin_amdgcn_readlane(c.off, rk + 1) <= tb) ++rk;
+        int base = __builtin_amdgcn_readlane(c.base, rk);
+        for (int k = rk + 1; k < 9; ++k) {
+          const int o = __builtin_amdgcn_readlane(c.off, k);
+          if (o >= tb + 64) break;
+          base = tc >= o ? __builtin_amdgcn_readlane(c.base, k) : base;
+        }
+        q[u] = spos[base + tc];
+        j[u] = sidx[base + tc];
+      }
     }
 #pragma unroll
-    for (int u = 0; u < CAND_BATCHES; ++u) f(t0 + 64 * u + lane, q[u], j[u]);
+    for (int u = 0; u < CAND_BATCHES; ++u)
+      if (t0 + 64 * u < c.total) f(t0 + 64 * u + lane, q[u], j[u]);
   }
 }
 
@@ -558,7 +560,7 @@ constexpr int FUSE_LIM = 512;
 // low words visited.
 // val NULL: a key's low word is its payload.
 template <int NT>
-__device__ __forceinline__ void select_cap(const uint64_t* key, const int32_t* val, uint32_t* js,
+__device__ __forceinline__ void select_cap_bits(const uint64_t* key, const int32_t* val, uint32_t* js,
                                            int n, int cap, int lane) {
   uint32_t kh[NT], kl[NT];
   int32_t vr[NT];
@@ -618,6 +620,107 @@ __device__ __forceinline__ void select_cap(const uint64_t* key, const int32_t* v
   }
 }
 
+// The same selection with fewer passes over the keys.  The high words are
+// bracketed, lo < cap-th smallest <= hi, and probed between them by
+// interpolation on the counts (two or three probes bring a bracket of 90 down to
+// a shell of a few, where the bits above decide one at a time, 25 or so: 575 ->
+// 449 us for 262,144 rows of 90 with the shorter candidate walk); the
+// keys of a bracket of at most SEL_RANK are then ranked exactly, both words,
+// one per lane.  Equal or nearly equal keys that no bracket of that size
+// separates (after SEL_PROBES) are left to the bits.  frac: the share of the
+// range [0, top] expected to hold the cap smallest of the n keys.
+constexpr int SEL_RANK = 32, SEL_PROBES = 8;
+template <int NT, bool FLOATS>
+__device__ __forceinline__ void select_cap(uint64_t* key, const int32_t* val, uint32_t* js, int n, int cap, int lane,
+                                           uint32_t top, float frac) {
+  uint32_t kh[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int u = lane + 64 * t;
+    kh[t] = u < n ? (uint32_t)(key[u] >> 32) : 0xFFFFFFFFu;
+  }
+  // counts at the ends of the bracket; every real key is at most top
+  // (keys past n count as above it, so an all-ones top leaves them to vm)
+  uint32_t lo = 0, hi = top;
+  int cl = 0, ch = n;
+  bool below = false;   // lo itself is a tested bound (cl keys at most lo); at first nothing is below
+  for (int it = 0; it < SEL_PROBES && ch - cl > SEL_RANK && ch != cap && hi - lo > 1; ++it) {
+    uint32_t mid;
+    if constexpr (FLOATS) {
+      const float fl = __uint_as_float(lo), fh = __uint_as_float(hi);
+      const float w = it == 0 ? frac : ((float)(cap - cl) + 0.5f) / (float)(ch - cl);
+      mid = __float_as_uint(fl + (fh - fl) * w);
+    } else {
+      const float w = it == 0 ? frac : ((float)(cap - cl) + 0.5f) / (float)(ch - cl);
+      mid = lo + (uint32_t)((float)(hi - lo) * w);
+    }
+    mid = __builtin_amdgcn_readfirstlane(mid);
+    mid = mid <= lo ? lo + 1 : mid >= hi ? hi - 1 : mid;
+    int c = 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) c += __popcll(__ballot(lane + 64 * t < n && kh[t] <= mid));
+    if (c >= cap) {
+      hi = mid;
+      ch = c;
+    } else {
+      lo = mid;
+      cl = c;
+      below = true;
+    }
+  }
+  const int m = ch - cl, need = cap - cl;   // keys of the bracket, and how many of them are kept
+  if (m > 64 && need != m) {
+    select_cap_bits<NT>(key, val, js, n, cap, lane);
+    return;
+  }
+  // the payloads, then the keys below the bracket to js and the bracket's keys
+  // and payloads to the front of the key array, one per lane
+  uint32_t kl[NT];
+  int32_t vr[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int u = lane + 64 * t;
+    kl[t] = u < n ? (uint32_t)key[u] : 0u;
+    vr[t] = val ? (u < n ? val[u] : 0) : (int32_t)kl[t];
+  }
+  wave_sync();   // every key is read; js and the bracket overwrite them
+  // js takes the first cap (at most 64) words, 256 bytes; the bracket's keys lie
+  // behind them (64 keys of 8 bytes at 256), their payloads behind those
+  uint64_t* bk = key + 32;
+  uint32_t* bv = reinterpret_cast<uint32_t*>(key + 96);
+  int s0 = 0, b0 = 0;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const bool in = lane + 64 * t < n, low = in && below && kh[t] <= lo, mid = in && !low && kh[t] <= hi;
+    const uint64_t ml = __ballot(low), mm = __ballot(mid);
+    const uint64_t before = (1ull << lane) - 1ull;
+    if (low) js[s0 + __popcll(ml & before)] = (uint32_t)vr[t];
+    if (mid) {
+      const int at = b0 + __popcll(mm & before);
+      if (need == m) {
+        js[cl + at] = (uint32_t)vr[t];
+      } else {
+        bk[at] = ((uint64_t)kh[t] << 32) | kl[t];
+        bv[at] = (uint32_t)vr[t];
+      }
+    }
+    s0 += __popcll(ml);
+    b0 += __popcll(mm);
+  }
+  if (need == m) return;
+  wave_sync();
+  const uint64_t mine = lane < m ? bk[lane] : ~0ull;
+  const uint32_t pay = lane < m ? bv[lane] : 0u;
+  const uint32_t mh = (uint32_t)(mine >> 32), mw = (uint32_t)mine;
+  int rank = 0;
+  for (int k = 0; k < m; ++k) {
+    const uint32_t oh = (uint32_t)__builtin_amdgcn_readlane((int)mh, k);
+    const uint32_t ow = (uint32_t)__builtin_amdgcn_readlane((int)mw, k);
+    rank += oh < mh || (oh == mh && ow < mw);
+  }
+  if (lane < m && rank < need) js[cl + rank] = pay;
+}
+
 // One wave per destination row, up to four rows per block (each wave with
 // its own lim x 12 bytes of shared memory): gather the sources that pass the
 // test, apply the cap (the cap smallest keys: (d2, j) or the hashed key), sort
@@ -670,14 +773,14 @@ __global__ __launch_bounds__(256) void k_nbr_fill(const float* __restrict__ pos,
   uint32_t* js = reinterpret_cast<uint32_t*>(key);   // kept sources (the key array reused as uint32 scratch)
   if (cap > 0 && n > cap && n <= 64 * SEL_PER_LANE) {
     switch ((n + 63) >> 6) {
-      case 1: select_cap<1>(key, val, js, n, cap, lane); break;
-      case 2: select_cap<2>(key, val, js, n, cap, lane); break;
-      case 3: select_cap<3>(key, val, js, n, cap, lane); break;
-      case 4: select_cap<4>(key, val, js, n, cap, lane); break;
-      case 5: select_cap<5>(key, val, js, n, cap, lane); break;
-      case 6: select_cap<6>(key, val, js, n, cap, lane); break;
-      case 7: select_cap<7>(key, val, js, n, cap, lane); break;
-      default: select_cap<8>(key, val, js, n, cap, lane); break;
+      case 1: select_cap_bits<1>(key, val, js, n, cap, lane); break;
+      case 2: select_cap_bits<2>(key, val, js, n, cap, lane); break;
+      case 3: select_cap_bits<3>(key, val, js, n, cap, lane); break;
+      case 4: select_cap_bits<4>(key, val, js, n, cap, lane); break;
+      case 5: select_cap_bits<5>(key, val, js, n, cap, lane); break;
+      case 6: select_cap_bits<6>(key, val, js, n, cap, lane); break;
+      case 7: select_cap_bits<7>(key, val, js, n, cap, lane); break;
+      default: select_cap_bits<8>(key, val, js, n, cap, lane); break;
     }
     n = cap;
   } else {
@@ -862,13 +965,18 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
   wave_sync();
   uint32_t* js = reinterpret_cast<uint32_t*>(key);  // kept sources, over the keys
   if (n > cap) {
+    // squared distances: the cap nearest of n in a ball of D dimensions lie within
+    // (cap / n)^(2/D) of its squared radius; hashed keys are uniform
+    const float share = (float)cap / (float)n;
+    const float frac = KNN && D == 3 ? __builtin_amdgcn_exp2f(0.6666667f * __builtin_amdgcn_logf(share)) : share;
+    const uint32_t top = KNN ? __float_as_uint(r2) : 0xFFFFFFFFu;
     switch ((n + 63) >> 6) {
-      case 1: select_cap<1>(key, val, js, n, cap, lane); break;
-      case 2: select_cap<2>(key, val, js, n, cap, lane); break;
-      case 3: select_cap<3>(key, val, js, n, cap, lane); break;
-      case 4: select_cap<4>(key, val, js, n, cap, lane); break;
-      case 5: case 6: select_cap<6>(key, val, js, n, cap, lane); break;
-      default: select_cap<8>(key, val, js, n, cap, lane); break;
+      case 1: select_cap<1, KNN>(key, val, js, n, cap, lane, top, frac); break;
+      case 2: select_cap<2, KNN>(key, val, js, n, cap, lane, top, frac); break;
+      case 3: select_cap<3, KNN>(key, val, js, n, cap, lane, top, frac); break;
+      case 4: select_cap<4, KNN>(key, val, js, n, cap, lane, top, frac); break;
+      case 5: case 6: select_cap<6, KNN>(key, val, js, n, cap, lane, top, frac); break;
+      default: select_cap<8, KNN>(key, val, js, n, cap, lane, top, frac); break;
     }
   } else if constexpr (KNN) {
     const uint32_t j = lane < n ? (uint32_t)key[lane] : 0u;   // n <= cap <= 64

@@ -171,6 +171,16 @@ CASES = {
     "sparse_8192_points": (lambda: _rand(8192, 2, 30), 8192, 0.004, 0, 0),
     "sparse_8193_points": (lambda: _rand(8193, 2, 31), 8193, 0.004, 0, 0),
     "8193_points_halo_random": (lambda: _rand(8193, 3, 32), 7000, 0.07, 6, 1),
+    # the cap among shells of equal and nearly equal distances (a lattice), among
+    # more equal distances than are ranked one per lane (coincident points, and
+    # nearly coincident ones), and one edge short of the row
+    "lattice3d_knn24": (lambda: np.stack(np.meshgrid(*[np.linspace(0, 1, 14)] * 3, indexing="ij"),
+                                         -1).reshape(-1, 3).astype(np.float32), 2744, 0.2, 24, 0),
+    "coincident_knn10": (lambda: np.repeat(_rand(20, 2, 35), 100, axis=0), 2000, 0.01, 10, 0),
+    "coincident_random10": (lambda: np.repeat(_rand(20, 2, 36), 100, axis=0), 2000, 0.01, 10, 1),
+    "near_coincident_knn40": (lambda: (np.repeat(_rand(10, 3, 37), 200, axis=0)
+                                       + 1e-7 * _rand(2000, 3, 38)).astype(np.float32), 2000, 0.01, 40, 0),
+    "complete_66_knn64": (lambda: _rand(66, 2, 39), 66, 5.0, 64, 0),
     # row counts scanned in one launch (up to 16,384 rows) and in two
     "2d_16384_rows": (lambda: _rand(16384, 2, 33), 16384, 0.02, 0, 0),
     "2d_16385_rows_knn": (lambda: _rand(16500, 2, 34), 16385, 0.03, 9, 0),
