@@ -2798,7 +2798,7 @@ BwdWs carve_bwd(const dsmp_layer_desc& d, int64_t n_dst, int64_t n_src, int64_t 
   w.p_w2 = c.take<float>((size_t)w.n2 * (d.h2 * d.h1 + d.h2));
   w.n1 = (int)(E > 0 ? (ceil_div(E, 64) < 2048 ? ceil_div(E, 64) : 2048) : 1);
   w.pc1 = E > 0 ? (E + w.n1 - 1) / w.n1 : 1;
-  w.p_w1 = c.take<float>((size_t)w.n1 * (d.h1 * de + d.h1));
+  w.p_w1 = c.take<float>((size_t)std::max(w.n1, 4) * (d.h1 * de + d.h1));   // k_da1_dw1: one per wave, so 4 or more
   w.total = c.used();
   return w;
 }

@@ -268,6 +268,29 @@ def test_node_terms_sliced_sums(env, algo, shape):
     _check_backward(c, "E=%d" % c.col.size)
 
 
+def test_backward_workspace_few_edges(env):
+    """The backward of a d = 128 layer with a handful of edges (its da1 pass
+    writes four partial sums, more than one per 64 edges) stays within the
+    workspace that was asked for."""
+    dm, lib, torch = env
+    announce("few edges, workspace end")
+    c = random_case(env, "bf16_128", n=40, D=3, r=0.15, seed=9)
+    assert 0 < c.col.size <= 64
+    lib.dsmp_set_edge_algorithm(dm.EDGE_AGGREGATE)
+    try:
+        c.forward()
+        _, _, bb = lib.dsmp_nnconv_workspace(c.desc, c.g)
+        ws = torch.full((bb + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+        gh, grads = lib.dsmp_nnconv_backward(c.desc, c.packed, c.g, c.t_attr, c.t_h, c.saved,
+                                             torch.from_numpy(c.G).cuda(), ws=ws[:bb])
+        assert bool((ws[bb:] == 0xA5).all())
+        ref = c.oracle_backward()
+        for k in GRAD_KEYS:
+            assert rel_err(grads[k].cpu().numpy(), ref[k], ref["allow"][k]) <= TOL["bf16"], k
+    finally:
+        lib.dsmp_set_edge_algorithm(dm.EDGE_AUTO)
+
+
 @pytest.mark.parametrize("name", sorted(FWD_CASES))
 def test_backward_parity(env, algo, name):
     kw = FWD_CASES[name]
