@@ -124,6 +124,15 @@ def gemm_slices(n_rows):
     return max(1, min(16, 2048 // waves))
 
 
+def dz_with_m(w, E, n, fused):
+    """Whether the library's backward takes da1 and dW2 from stored da2 rows and
+    recomputes z1 (dz_with_m in nnconv_bwd.hip)."""
+    if w.dtype != "bf16" or fused:
+        return False
+    shape = (w.d, w.H1, w.H2)
+    return shape == (128, 256, 256) or (shape == (64, 128, 128) and n * w.H2 * w.d * 2 > 256 << 20 and E <= 22 * n)
+
+
 def work_model(w, E, n_src, fused=False, n_dst=None):
     """Algorithmic work of one launch of each kernel class: flops and the
     compulsory HBM bytes (every input read once, every output written once).
@@ -134,9 +143,9 @@ def work_model(w, E, n_src, fused=False, n_dst=None):
     esz = 2 if w.dtype == "bf16" else 4
     kt = (H2 + 1) * d                  # length of a segment-sum row
     mask = (H1 + H2) // 8              # ReLU mask bytes per edge
-    # z1 rows are kept for the backward unless it recomputes them: the fused
-    # edge-gradient pass, or the dW2 pass at d = 128, h1 = h2 = 256 (bf16)
-    keeps_z1 = not fused and not (w.dtype == "bf16" and (d, H1, H2) == (128, 256, 256))
+    # z1 rows are kept for the backward unless it recomputes them: in the fused
+    # edge-gradient pass, or in the dW2 pass
+    keeps_z1 = not fused and not dz_with_m(w, E, n, fused)
     idx = 8                            # two int32 indices per edge
     attr = 2 * (D + 1) * 4             # node attribute rows of both ends
     m = {
@@ -146,7 +155,7 @@ def work_model(w, E, n_src, fused=False, n_dst=None):
         "edge_dh": (2 * E * (H2 + 1) * d * d, E * (idx + d * esz + H2 * esz) + n_src * d * 4),
         # aggregate form
         # the split attributes (32 bytes) are stored for the unfused backward, z1
-        # too where the dW2 pass does not recompute it (d = 128, h = 256)
+        # too where the dW2 pass does not recompute it
         "edge_mlp": (2 * E * (de * H1 + H1 * H2),
                      E * (idx + attr + H2 * esz + mask + (0 if fused else 32) + (H1 * esz if keeps_z1 else 0))),
         "outer_fwd": (2 * E * H2 * d, E * (4 + H2 * esz + d * esz) + n * kt * esz),
@@ -170,7 +179,7 @@ def agg_work(w, E, n_src, fused=False):
     esz = 2 if w.dtype == "bf16" else 4
     kt = (H2 + 1) * d
     mask = (H1 + H2) // 8
-    dz_m = w.dtype == "bf16" and not fused and (d, H1, H2) == (128, 256, 256)
+    dz_m = dz_with_m(w, E, n, fused)
     if fused:
         dz = (2 * E * (d * H2 + H1 * H2 + H1 * H2 + H1 * de),
               n * H2 * d * esz + E * (4 + d * esz + mask + 2 * (D + 1) * 4))
@@ -526,6 +535,8 @@ def main():
     fused = agg and not ("dW2" in prof and prof["dW2"][1] > 0)
     if infer:   # no backward ran: the forward's stores follow the shape's backward
         fused = agg and w.dtype == "bf16" and w.H1 == w.H2 and w.H1 in (64, 128)
+        nb = max(1, sum(1 for st in pipe.inf.stats if st[1] > 0))
+        fused = fused and not dz_with_m(w, E / nb, sum(st[1] for st in pipe.inf.stats) / nb, False)
     if infer:
         # every box is a graph of its own and each layer launch runs over one
         # box: a launch's work is the boxes' total over the number of boxes

@@ -118,15 +118,15 @@ struct LdsStage {
 constexpr int LDS_COPY_STREAM = 2;
 
 // Copy n16 contiguous 16-byte units from global memory to contiguous LDS
-// (each wave-wide load one contiguous kilobyte).
-template <int POLICY = 0>
+// (each wave-wide load one contiguous kilobyte), by a workgroup of NT threads.
+template <int POLICY = 0, int NT = 256>
 __device__ __forceinline__ void lds_copy_async(const unsigned char* src, unsigned char* dst, int n16) {
   const int tid = (int)threadIdx.x, wbase = tid & ~63;
-  for (int i = 0; i * 256 < n16; ++i) {
-    const int U = i * 256 + tid;
+  for (int i = 0; i * NT < n16; ++i) {
+    const int U = i * NT + tid;
     if (U < n16)
       __builtin_amdgcn_global_load_lds((gbl_void_t*)(src + (size_t)U * 16),
-                                       (lds_void_t*)(dst + (size_t)(i * 256 + wbase) * 16), 16, 0, POLICY);
+                                       (lds_void_t*)(dst + (size_t)(i * NT + wbase) * 16), 16, 0, POLICY);
   }
 }
 
@@ -434,12 +434,13 @@ dsmp_status check_graph(dsmp_handle* h, const dsmp_graph* g, bool need_csc);
 int layer_attr_width(const dsmp_layer_desc& d);
 
 // Whether the backward of an aggregate-form layer runs the fused edge-gradient
-// pass (bf16, h1 = h2 in {64, 128}, d in {32, 64}).  That pass recomputes z1
-// and the edge attributes, so the forward then stores neither.
-bool fused_edge_grads(const dsmp_layer_desc& d);
-// bf16 aggregate layers at d = 128, h1 = h2 = 256: dz with the feature-gradient
-// terms in one pass, da1 with the dW1 sums, dW2 with z1 recomputed
-bool dz_with_m(const dsmp_layer_desc& d, bool agg);
+// pass (bf16, h1 = h2 in {64, 128}, d in {32, 64}, and not dz_with_m).  That pass
+// recomputes z1 and the edge attributes, so the forward then stores neither.
+bool fused_edge_grads(const dsmp_layer_desc& d, int64_t n_dst, int64_t E);
+// bf16 aggregate layers at d = 128, and large ones of low degree at d = 64: dz
+// with the feature-gradient terms in one pass, da1 with the dW1 sums, dW2 with z1
+// recomputed
+bool dz_with_m(const dsmp_layer_desc& d, bool agg, int64_t n_dst, int64_t E);
 
 // Aggregate form of the edge contraction (nnconv_agg.hip).
 bool use_aggregate(const dsmp_handle* h, const dsmp_layer_desc& d, int64_t n_dst, int64_t E);

@@ -1713,26 +1713,30 @@ __global__ __launch_bounds__(W8 ? 512 : 256, W8 ? 1 : 2) void k_bwd_dW2_tr(W2Arg
   if (split == 0 && tid < H2) out[H2 * H1 + kperm<__bf16>(tid)] = bsum;
 }
 
-// dW2 and db2 where the forward kept no z1 rows (d = 128, h1 = h2 = 256):
+// dW2 and db2 where the forward kept no z1 rows (dz_with_m layers, h1 = h2):
 // z1 = ReLU(W1 x + b1) of each chunk of edges is recomputed on the matrix
 // cores from the saved bf16 high and low parts of x, as the fused
 // edge-gradient pass does (W1h xh + W1h xl + W1l xh + b1h + b1l with fp32
 // accumulation, within about 2^-16 of the forward's fp32 chain), rounded to
 // bf16 into the chunk's z1 rows in LDS; the dW2 products, the waves' tiles
 // and the outputs are those of k_bwd_dW2_tr with eight waves.  Wave w forms
-// the z1 row blocks 2 (w % 4), 2 (w % 4) + 1 of edge block w / 4 of the chunk.
+// the ZQ = h1 / 128 z1 row blocks from ZQ (w % 4) of edge block w / 4 of the chunk.
+// Bound by the reads of da2 and x (288 bytes per edge at h = 128: 82 us over
+// 1,079,000 edges, 3.8 TB/s; two workgroups share a CU there).
 // Two statically distinct chunk buffers alternate in code; the next chunk's
 // attribute rows are loaded ahead of its da2 copy.
 template <int H1, int H2>
 __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
-  using S = W2TrTiles<H1, H2, true>;
+  // waves along j, k and j tiles per wave, z1 row blocks per wave
+  constexpr int JG = H1 == 256 ? 2 : 4, KT_W = 2, JT_W = H1 / 32 / JG, ZQ = H1 / 128;
   using TS = W2TrShape<H1, H2>;
   using M = MT<__bf16>;
   constexpr int ECH = TS::ECH;
-  static_assert(ECH == 64 && H1 == 256, "two 32-edge blocks per chunk, eight 32-row blocks of z1 per block");
+  static_assert(ECH == 64 && H1 == H2 && (H1 == 128 || H1 == 256) && 8 / JG * KT_W * 32 == H2,
+                "two 32-edge blocks per chunk, eight waves over all tiles");
   __shared__ __align__(16) unsigned char XA[TS::BUF], XB[TS::BUF];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, hh = lane >> 5, l32 = lane & 31;
-  const int kt0 = (wv / 2) * 2, jt0 = (wv % 2) * 4, sb = wv / 4;
+  const int kt0 = (wv / JG) * KT_W, jt0 = (wv % JG) * JT_W, sb = wv / 4;
   const int64_t e_begin = (int64_t)blockIdx.x * a.per_chunk;
   int64_t e_end = e_begin + a.per_chunk;
   if (e_end > a.E) e_end = a.E;
@@ -1740,13 +1744,13 @@ __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
   // A operands of the z1 products: row R of block zb holds the layer-1
   // weights of stored position (2 zb + i/8)*16 + hr*8 + i%8, R = 8(i/4) +
   // 4 hr + i%4; K slots 0..7 W1h, 8..15 W1h, 16..23 W1l, 24 b1h, 25 b1l
-  bf16x8 wa[2], wb[2];
+  bf16x8 wa[ZQ], wb[ZQ];
   {
     const float* w1 = reinterpret_cast<const float*>(a.w1l);
     const float* b1 = reinterpret_cast<const float*>(a.b1l);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int zb = 2 * (wv % 4) + q;
+    for (int q = 0; q < ZQ; ++q) {
+      const int zb = ZQ * (wv % 4) + q;
       const int R = l32, i = 4 * (R / 8) + R % 4, hr = (R % 8) / 4;
       const int pos = (2 * zb + i / 8) * 16 + hr * 8 + i % 8;
       const int hn = ((pos % 16) / 8) * (H1 / 2) + (pos / 16) * 8 + pos % 8;
@@ -1770,11 +1774,11 @@ __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
       wb[q] = pack_frag<__bf16>(v1);
     }
   }
-  f32x16 acc[S::KT_W][S::JT_W];
+  f32x16 acc[KT_W][JT_W];
 #pragma unroll
-  for (int kk = 0; kk < S::KT_W; ++kk)
+  for (int kk = 0; kk < KT_W; ++kk)
 #pragma unroll
-    for (int jj = 0; jj < S::JT_W; ++jj) acc[kk][jj] = f32x16{};
+    for (int jj = 0; jj < JT_W; ++jj) acc[kk][jj] = f32x16{};
   float bsum = 0.0f;
   const int nch = (int)((e_end - e_begin + ECH - 1) / ECH);
   typename TS::DS sd;
@@ -1798,8 +1802,8 @@ __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
     const bf16x8 xb1 = hh ? pack_frag<__bf16>(one) : xb0;   // [xh | 1 1 0 ...]
     unsigned char* zrow = buf + TS::DB + (32 * sb + l32) * TS::ZS::PITCH;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int zb = 2 * (wv % 4) + q;
+    for (int q = 0; q < ZQ; ++q) {
+      const int zb = ZQ * (wv % 4) + q;
       f32x16 Z = f32x16{};
       Z = M::mma(wa[q], xb0, Z);
       Z = M::mma(wb[q], xb1, Z);
@@ -1818,9 +1822,9 @@ __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
     if (tid < H2)
       for (int e = 0; e < cnt; ++e) bsum += (float)*reinterpret_cast<const __bf16*>(cur + e * TS::DS::PITCH + tid * 2);
     for (int ks = 0; ks < (cnt + 15) / 16; ++ks) {
-      bf16x8 A[S::KT_W];
+      bf16x8 A[KT_W];
 #pragma unroll
-      for (int kk = 0; kk < S::KT_W; ++kk) {
+      for (int kk = 0; kk < KT_W; ++kk) {
         A[kk] = lds_frag_rows(cur, TS::DS::PITCH, ks * 16, (kt0 + kk) * 32);
         if (ks * 16 + 16 > cnt) {
 #pragma unroll
@@ -1829,10 +1833,10 @@ __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
         }
       }
 #pragma unroll
-      for (int jj = 0; jj < S::JT_W; ++jj) {
+      for (int jj = 0; jj < JT_W; ++jj) {
         const bf16x8 B = lds_frag_rows(cur + TS::DB, TS::ZS::PITCH, ks * 16, (jt0 + jj) * 32);
 #pragma unroll
-        for (int kk = 0; kk < S::KT_W; ++kk) acc[kk][jj] = M::mma(A[kk], B, acc[kk][jj]);
+        for (int kk = 0; kk < KT_W; ++kk) acc[kk][jj] = M::mma(A[kk], B, acc[kk][jj]);
       }
     }
   };
@@ -1866,10 +1870,10 @@ __global__ __launch_bounds__(512, 1) void k_bwd_dW2_rz(W2Args a) {
   float* out = a.part + (size_t)blockIdx.x * (H2 * H1 + H2);
   // tile rows and columns are stored-order positions; map them back to (k, j)
 #pragma unroll
-  for (int jj = 0; jj < S::JT_W; ++jj) {
+  for (int jj = 0; jj < JT_W; ++jj) {
     const int j = kperm<__bf16>((jt0 + jj) * 32 + l32);
 #pragma unroll
-    for (int kk = 0; kk < S::KT_W; ++kk)
+    for (int kk = 0; kk < KT_W; ++kk)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int k = kperm<__bf16>((kt0 + kk) * 32 + 8 * (i / 4) + 4 * hh + (i % 4));
@@ -2370,9 +2374,10 @@ __global__ __launch_bounds__(256) void k_dh_gather(int64_t n_src, int64_t n_dst,
 // ------------------------------------------------------------ dz and feature-gradient terms in one pass
 // The two per-edge products that read U_i, dz_e = U_i h_j and
 // m_e = U~_i^T z~_e, in one pass over each destination's edges (bf16 layers
-// whose kernel-MLP gradients are not fused, h2 = 256), so that U is read from
-// HBM once for both.  U_i and g_i are copied to LDS as they stand (direct
-// global-to-LDS loads, double-buffered over destinations).  Of the four
+// whose kernel-MLP gradients are not fused), so that U is read from HBM once for
+// both: at d = 64, 100,000 destinations of 10.8 edges, 530 us (1.64 GB of U,
+// 0.8 GB of rows), where the fused pass and k_dh_u take 472 and 477 us.  U_i and g_i are copied to LDS as they stand (direct
+// global-to-LDS loads, double-buffered over destinations).  Of the d / 32
 // waves, wave w takes, for every 32-edge tile of the destination, the two
 // 32-neuron tiles 2w, 2w + 1 of dz (A = U_i fragments read from LDS as
 // stored, B = h_j rows), which it masks with the forward's ReLU bits of z
@@ -2390,16 +2395,16 @@ struct DzDhuArgs {
 template <int DL, int H1, int H2>
 struct DzDhuShape {
   static constexpr int UB = H2 * DL * 2, GB = DL * 2, BUF = UB + GB, LDS = 2 * BUF;
-  static_assert(UB % (256 * 16) == 0 && GB % 16 == 0 && GB / 16 <= 256, "U_i whole rounds, g_i one partial round");
+  static_assert(UB % (2 * DL * 16) == 0 && GB % 16 == 0 && GB / 16 <= 2 * DL, "U_i whole rounds, g_i one partial round");
 };
 
 template <int DL, int H1, int H2>
-__global__ __launch_bounds__(256) void k_dz_dh_u(DzDhuArgs a) {
+__global__ __launch_bounds__(2 * DL, DL == 64 ? 2 : 1) void k_dz_dh_u(DzDhuArgs a) {
   using S = DzDhuShape<DL, H1, H2>;
   using M = MT<__bf16>;
-  constexpr int SKD = DL / 16, SK2 = H2 / 16, PT = DL / 32, KT = H2 / 32, KTW = KT / 4;
+  constexpr int SKD = DL / 16, SK2 = H2 / 16, PT = DL / 32, NW = PT, KT = H2 / 32, KTW = KT / NW;
   constexpr int MW1 = H1 / 64, MW2 = H2 / 64, MROW = (H1 + H2) / 8;
-  static_assert(PT == 4 && KTW == 2, "one column tile of p and two neuron tiles per wave");
+  static_assert(KTW == 2, "one column tile of p and two neuron tiles per wave");
   // two statically distinct buffers: the compiler can then see that the
   // copies into one never alias the reads of the other, and does not wait
   // for the copies before every LDS read
@@ -2504,8 +2509,8 @@ __global__ __launch_bounds__(256) void k_dz_dh_u(DzDhuArgs a) {
   load_ops(pa, pb, 0, first_col(pa, pb), opsA);
   int32_t c1 = first_col(pa1, pb1);
   // U_i is read once, here: streaming copies
-  lds_copy_async<LDS_COPY_STREAM>(d.U + (size_t)i0 * S::UB, XA, S::UB / 16);
-  lds_copy_async(d.gT + (size_t)i0 * S::GB, XA + S::UB, S::GB / 16);
+  lds_copy_async<LDS_COPY_STREAM, 64 * NW>(d.U + (size_t)i0 * S::UB, XA, S::UB / 16);
+  lds_copy_async<0, 64 * NW>(d.gT + (size_t)i0 * S::GB, XA + S::UB, S::GB / 16);
   // one destination: its U_i and g_i in Xc (copied one step earlier), its
   // operands in cur; the next destination's copies go to Xn, its operands to
   // nxt.  The loop alternates the two (buffers, operand sets) in code, so no
@@ -2525,8 +2530,8 @@ __global__ __launch_bounds__(256) void k_dz_dh_u(DzDhuArgs a) {
       // unconditional (the last step copies its own U_i again): the count of
       // operations after the operand loads then includes these copies
       const int64_t inext = i + G < d.n_dst ? i + G : i;
-      lds_copy_async<LDS_COPY_STREAM>(d.U + (size_t)inext * S::UB, Xn, S::UB / 16);
-      lds_copy_async(d.gT + (size_t)inext * S::GB, Xn + S::UB, S::GB / 16);
+      lds_copy_async<LDS_COPY_STREAM, 64 * NW>(d.U + (size_t)inext * S::UB, Xn, S::UB / 16);
+      lds_copy_async<0, 64 * NW>(d.gT + (size_t)inext * S::GB, Xn + S::UB, S::GB / 16);
     }
     asm volatile("" ::: "memory");   // the copies stay ahead of the tile's stores
     __builtin_amdgcn_sched_barrier(0);
@@ -2588,7 +2593,7 @@ struct Da1Shape {
 };
 
 template <int H1, int H2>
-__global__ __launch_bounds__(256) void k_da1_dw1(Da1Args a) {
+__global__ __launch_bounds__(256, H1 == 128 ? 2 : 1) void k_da1_dw1(Da1Args a) {
   using SA = DzAggShape<__bf16, H1, H2>;
   using S = Da1Shape<H1, H2>;
   using M = MT<__bf16>;
@@ -2823,15 +2828,15 @@ dsmp_status run_edge_grads(dsmp_handle* h, const DzArgs& dz, const W3Args& w3, c
       if ((st = launch_u_gemm<T, DL, H2>(h, ua)) != DSMP_OK) return st;
     }
     if (fm) {
-      if constexpr (sizeof(T) == 2 && DL == 128 && H1 == 256 && H2 == 256) {
+      if constexpr (sizeof(T) == 2 && DL >= 64) {
         {
           // dz (masked into da2) and the feature-gradient terms from one read of U
           auto kf = k_dz_dh_u<DL, H1, H2>;   // static LDS: two U_i + g_i buffers
           int per_cu = 0;
-          DSMP_HIP(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kf, 256, 0));
+          DSMP_HIP(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kf, 2 * DL, 0));
           const int64_t grid = std::min<int64_t>(dz.n_dst, (int64_t)h->n_cu * std::max(per_cu, 1));
           ProfScope prof(h, DSMP_K_DZ);
-          if (grid > 0) hipLaunchKernelGGL(kf, dim3((unsigned)grid), dim3(256), 0, s, *fm);
+          if (grid > 0) hipLaunchKernelGGL(kf, dim3((unsigned)grid), dim3(2 * DL), 0, s, *fm);
           DSMP_LAUNCHED(h, "dz and feature-gradient terms from U");
         }
         {
@@ -2849,7 +2854,7 @@ dsmp_status run_edge_grads(dsmp_handle* h, const DzArgs& dz, const W3Args& w3, c
           *n1_used = (int)(4 * grid);
         }
       } else {
-        return fail(h, DSMP_UNSUPPORTED, "dz with the feature-gradient terms is built for d = 128, h = 256 only");
+        return fail(h, DSMP_UNSUPPORTED, "dz with the feature-gradient terms is built for d = 64 and 128 only");
       }
     } else {
     using SA = DzAggShape<T, H1, H2>;
@@ -2888,12 +2893,17 @@ dsmp_status run_edge_grads(dsmp_handle* h, const DzArgs& dz, const W3Args& w3, c
     if (nchunk < 1) nchunk = 1;
     if constexpr (sizeof(T) == 2) {
       using TS = W2TrShape<H1, H2>;
-      if constexpr (S::NSPLIT > 1 && H1 == 256 && H2 == 256) {
+      if constexpr (H1 >= 128) {
         if (w2.z1E == nullptr) {   // z1 recomputed from the split attributes
           auto k2 = k_bwd_dW2_rz<H1, H2>;
           ProfScope prof(h, DSMP_K_DW2);
           hipLaunchKernelGGL(k2, dim3(nchunk), dim3(512), 0, s, w2);
-        } else {
+          DSMP_LAUNCHED(h, "dW2");
+          return DSMP_OK;
+        }
+      }
+      if constexpr (S::NSPLIT > 1 && H1 == 256 && H2 == 256) {
+        {
           auto k2 = k_bwd_dW2_tr<H1, H2, true>;
           if ((st = set_lds(h, k2, TS::LDS)) != DSMP_OK) return st;
           ProfScope prof(h, DSMP_K_DW2);
@@ -2996,15 +3006,24 @@ void launch_node_kernels(dsmp_handle* h, const BNodeArgs& na, int64_t n_dst, con
 }  // namespace
 
 namespace dsmp {
-// Where the kernel-MLP gradients are not fused (bf16, d = 128, h1 = h2 = 256)
-// the dz pass also forms the feature-gradient terms (k_dz_dh_u), the da1 pass
-// the dW1 sums, and the dW2 pass recomputes z1 (the forward keeps no z1 rows).
-bool dz_with_m(const dsmp_layer_desc& d, bool agg) {
-  return agg && d.dtype == DSMP_BF16 && d.d == 128 && d.h1 == 256 && d.h2 == 256;
+// Where the kernel-MLP gradients are not fused (bf16) the dz pass also forms
+// the feature-gradient terms (k_dz_dh_u), the da1 pass the dW1 sums, and the dW2
+// pass recomputes z1 (the forward keeps no z1 rows): d = 128, and d = 64 where
+// reading U once instead of twice is worth passing da2 (256 bytes per edge,
+// written once and read twice) and the attributes through memory: U past the
+// 256 MB last-level cache, and at most 22 edges per destination.  Layer
+// forward and backward, fused against this: 100,000 nodes of 10.8 edges 2620 and
+// 2410 us; 40,000 of 11.9, 16.8, 21.8, 27.2: 1120 and 1050, 1199 and 1150, 1283
+// and 1266, 1388 and 1389; 30,011 of 21: 995 and 971; 8,192 of 13.2: 292 and 303.
+bool dz_with_m(const dsmp_layer_desc& d, bool agg, int64_t n_dst, int64_t E) {
+  if (!agg || d.dtype != DSMP_BF16) return false;
+  if (d.d == 128) return d.h1 == 256 && d.h2 == 256;
+  return d.d == 64 && d.h1 == 128 && d.h2 == 128 && n_dst * d.h2 * d.d * 2 > (256ll << 20) && E <= 22 * n_dst;
 }
 
-bool fused_edge_grads(const dsmp_layer_desc& d) {
-  return d.dtype == DSMP_BF16 && d.h1 == d.h2 && (d.h1 == 64 || d.h1 == 128) && (d.d == 32 || d.d == 64);
+bool fused_edge_grads(const dsmp_layer_desc& d, int64_t n_dst, int64_t E) {
+  return d.dtype == DSMP_BF16 && d.h1 == d.h2 && (d.h1 == 64 || d.h1 == 128) && (d.d == 32 || d.d == 64) &&
+         !dz_with_m(d, true, n_dst, E);
 }
 }  // namespace dsmp
 
@@ -3081,7 +3100,7 @@ extern "C" dsmp_status dsmp_nnconv_backward(dsmp_handle* h, const dsmp_layer_des
   ea.zE = const_cast<unsigned char*>(sv + sl.zE);
   ea.z1E = nullptr;
   ea.out_direct = w.dh_direct; ea.out_part = w.dh_part;
-  const bool dhu = dh_from_u(d, agg), dzm = dz_with_m(d, agg);
+  const bool dhu = dh_from_u(d, agg), dzm = dz_with_m(d, agg, n_dst, E);
   if (dhu) {
     // after the kernel-MLP gradients, from U (below)
   } else if (agg) {
@@ -3111,7 +3130,7 @@ extern "C" dsmp_status dsmp_nnconv_backward(dsmp_handle* h, const dsmp_layer_des
   // kernel-MLP gradients
   int nfused = 0;   // workgroups of the fused edge-gradient pass (their partials replace dW2's and dW1's)
   int n1da = 0;     // dW1 partials of the da1 pass (dz_with_m)
-  if (E > 0 && agg && fused_edge_grads(d)) {
+  if (E > 0 && agg && fused_edge_grads(d, n_dst, E)) {
     DzArgs dz{E, g->col, g->dst, hin, w.gF, pk, L, sv + sl.zE, sv + sl.zmask, w.da2E, w.da1E,
               w.U, w.gT, n_dst, g->row_ptr};
     EdgeGradArgs eg{dz, node_attr, d.dim, d.attr_mode, de, grads->dattr ? w.da1E : nullptr, w.p_w2, w.p_w1};

@@ -291,6 +291,52 @@ def test_backward_workspace_few_edges(env):
         lib.dsmp_set_edge_algorithm(dm.EDGE_AUTO)
 
 
+def test_backward_unfused_narrow(env):
+    """d = 64 where U exceeds the last-level cache and the mean degree is low: the
+    dz pass with the feature-gradient terms, da1 and dW2 from stored da2 rows
+    (16,390 destinations, rows of up to 45 edges and empty ones), and the node
+    attribute gradient from its da1 rows."""
+    dm, lib, torch = env
+    n, D = 16390, 2
+    announce("unfused narrow backward", n)
+    g = np.random.default_rng(77)
+    rows = np.unique(np.concatenate([g.choice(n - 64, 100, replace=False), np.arange(n - 30, n)]))
+    c = random_case(env, "bf16_64", n=n, D=D, r=0.0119, attr_mode=1, seed=78)   # about 7 edges on average
+    # a crowd of 46 among the sampled rows, one destination with none
+    pos = g.uniform(0, 1, (n, D)).astype(np.float32)
+    pos[rows[:46]] = 0.5 + 1e-4 * g.uniform(0, 1, (46, D)).astype(np.float32)
+    pos[rows[50]] = 5.0
+    c = Case(env, pos, c.attr, c.h, n, 0.0119, 0, c.P, "bf16", D, 64, 128, 128, 0, 1, 1, np.zeros_like(c.G), rows)
+    c.G[rows] = g.normal(0, 1, (rows.size, 64)).astype(np.float32)
+    deg = np.diff(c.rp)
+    assert c.col.size <= 22 * n and deg[rows].max() > 32 and deg[rows].min() == 0
+    grads = {k: torch.empty(v.shape, dtype=torch.float32, device="cuda")
+             for k, v in (("d" + q, w) for q, w in c.P.items())}
+    grads["dattr"] = torch.empty(n, D + 1, dtype=torch.float32, device="cuda")
+    lib.dsmp_set_edge_algorithm(dm.EDGE_AGGREGATE)
+    try:
+        c.forward()
+        lib.dsmp_profile_reset()
+        lib.dsmp_profile_enable(True)
+        gh, grads = lib.dsmp_nnconv_backward(c.desc, c.packed, c.g, c.t_attr, c.t_h, c.saved,
+                                             torch.from_numpy(c.G).cuda(), grads=grads)
+        assert lib.dsmp_profile_read()["da1"][1] == 1
+    finally:
+        lib.dsmp_profile_enable(False)
+        lib.dsmp_set_edge_algorithm(dm.EDGE_AUTO)
+    ref = c.oracle_backward()
+    assert rel_err(gh.cpu().numpy(), ref["grad_h"], ref["allow"]["grad_h"]) <= TOL["bf16"]
+    for k in GRAD_KEYS:
+        assert rel_err(grads[k].cpu().numpy(), ref[k], ref["allow"][k]) <= TOL["bf16"], k
+    dst = org.dst_of_edges(c.rp)
+    want, allow = np.zeros((n, D + 1)), np.zeros((n, D + 1))
+    np.add.at(want, dst, ref["grad_x"])
+    np.add.at(want, c.col, -ref["grad_x"])
+    np.add.at(allow, dst, ref["allow"]["grad_x"])
+    np.add.at(allow, c.col, ref["allow"]["grad_x"])
+    assert rel_err(grads["dattr"].cpu().numpy(), want, allow) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("name", sorted(FWD_CASES))
 def test_backward_parity(env, algo, name):
     kw = FWD_CASES[name]
