@@ -319,6 +319,38 @@ __device__ __forceinline__ float relu_mask(float v, uint32_t& word, int bit) {
   return z;
 }
 
+// ReLU of eight values as one bf16 fragment, rounded first and clamped on pairs
+// (the same bits as clamping first: rounding keeps the sign).
+__device__ __forceinline__ bf16x8 relu_pack(const float* v) {
+  typedef short s16x2 __attribute__((ext_vector_type(2)));
+  uint4 u = __builtin_bit_cast(uint4, pack_frag<__bf16>(v));
+  uint32_t* w = reinterpret_cast<uint32_t*>(&u);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    w[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, w[i]), s16x2{0, 0}));
+  return __builtin_bit_cast(bf16x8, u);
+}
+
+// relu_pack with the mask bits of the eight values added to half a mask word
+// (a 16-bit half, bits bit .. bit + 7, bit 0 or 8): four instructions for two
+// values, where clamping, masking and rounding one by one takes seven.  A
+// positive value too small for bf16 counts as zero, as its z does.
+__device__ __forceinline__ bf16x8 relu_pack_mask(const float* v, uint32_t& half, int bit) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  const bf16x8 f = relu_pack(v);
+  const uint4 u = __builtin_bit_cast(uint4, f);
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(&u);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t on;   // 1 in each half that is not zero
+    asm("v_pk_min_u16 %0, %1, 1 op_sel_hi:[1,0]" : "=v"(on) : "v"(w[i]));
+    const int b = bit + 2 * i;
+    half = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, on),
+                                  u16x2{(unsigned short)(1u << b), (unsigned short)(2u << b)}, half, false);
+  }
+  return f;
+}
+
 // p[0] + p[stride] + ... + p[(n-1) stride], added in index order starting
 // from +0 (the same bits as the plain loop), with the loads issued eight at a
 // time ahead of their additions instead of one load-wait-add per term.

@@ -629,6 +629,38 @@ struct MlpShape {
   static constexpr int MW = H / 64;                 // mask words per lane half and layer
 };
 
+// Stores 128 bytes of each of 32 rows as whole cache lines: f[k][j] of lane (i,
+// h) is the 16 bytes at 64 k + 32 j + 16 h of row i.  Rows 0..15 and 16..31
+// change places between the two j (lanes 16 apart), then rows 8 apart between
+// the two k, so that eight lanes hold the eight pieces of a row; as they stand
+// a store would touch 32 lines for 32 bytes each.
+__device__ __forceinline__ void store_z_lines(uint4 (&f)[2][2], unsigned char* base, int pitch) {
+  uint32_t(*w)[2][4] = reinterpret_cast<uint32_t(*)[2][4]>(&f[0][0]);
+  const int lane = threadIdx.x & 63;
+  uint32_t x[2][2][4];   // [rows 16 * .][rows 8 * .]
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    uint32_t v[2][2];   // [tile][rows 16 * .]
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const auto r = __builtin_amdgcn_permlane16_swap(w[k][0][d], w[k][1][d], false, false);
+      v[k][0] = r[0];
+      v[k][1] = r[1];
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {   // row_ror:8, into lanes 8..15 and 0..7 of each row of 16
+      x[r][0][d] = __builtin_amdgcn_update_dpp(v[0][r], v[1][r], 0x128, 0xf, 0xc, false);
+      x[r][1][d] = __builtin_amdgcn_update_dpp(v[1][r], v[0][r], 0x128, 0xf, 0x3, false);
+    }
+  }
+  unsigned char* p = base + (lane & 7) * pitch + ((lane >> 3) & 1) * 64 + ((lane >> 4) & 1) * 32 + (lane >> 5) * 16;
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      *reinterpret_cast<uint4*>(p + (16 * r + 8 * q) * pitch) = make_uint4(x[r][q][0], x[r][q][1], x[r][q][2], x[r][q][3]);
+}
+
 template <int H, bool SPLIT>
 __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void k_edge_mlp(EdgeArgs a,
                                                                                          int64_t ntiles) {
@@ -642,41 +674,54 @@ __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void 
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, l32 = lane & 31;
   const unsigned char* P = a.packed;
 
-  // W2, W1 and the biases to LDS, once per workgroup
-  {
-    constexpr int NU = H * 2 / 16;
-    const uint4* src = reinterpret_cast<const uint4*>(P + a.L.w2p);
-    for (int U = tid; U < H * NU; U += 64 * S::WAVES)
-      *reinterpret_cast<uint4*>(w2s + (U / NU) * S::W2B + (U % NU) * 16) = src[U];
-    const uint4* w1l = reinterpret_cast<const uint4*>(P + a.L.w1l);
-    for (int U = tid; U < 2 * H; U += 64 * S::WAVES) reinterpret_cast<uint4*>(w1s)[U] = w1l[U];
-    const float* b1l = reinterpret_cast<const float*>(P + a.L.b1l);
-    const float* b2 = reinterpret_cast<const float*>(P + a.L.b2);
-    for (int U = tid; U < H; U += 64 * S::WAVES) {
-      b1s[U] = b1l[U];
-      b2s[U] = b2[U];
-    }
-  }
-  // Layer-1 A operand: W1[32 rt + l32][2 ks + hh] from the packed halves
-  // (neuron 32c + r sits in half (r/4)%2 at position 16c + 4(r/8) + r%4).
-  const int nks = attr_slots(a.dim, a.attr_mode) / 2;
-  const float* w1a = w1s + ((((l32 >> 2) & 1) * (H / 2) + 4 * (l32 >> 3) + (l32 & 3)) * 8 + hh);
-  __syncthreads();
-
   const int64_t stride = (int64_t)gridDim.x * S::WAVES;
   int64_t tile = (int64_t)blockIdx.x * S::WAVES + (tid >> 6);
-  if (tile >= ntiles) return;
-  // Loads run a tile ahead: a tile's attribute rows, and the ids of the tile
-  // after it, are issued before the stores of the tile in hand, so waiting
-  // for them never waits for those stores (loads and stores retire in one
-  // in-order count).  Lanes past E read edge 0 and store into the padding
-  // rows of the last tile.
   const int rw = a.dim + 1;
   const float* na = a.node_attr;
   auto eid = [&](int64_t t) -> int64_t {
     const int64_t e = t * 32 + l32;
     return e < a.E ? e : 0;
   };
+  // W2, W1 and the biases to LDS, once per workgroup: every load goes out
+  // before the first is waited for, the ids of the wave's first two tiles ahead
+  // of them (one load and wait per 16 bytes and the ids after the copy took half
+  // the time of a launch with one tile per wave: 18.4 us for 39,000 edges, ...)
+  const int64_t e0 = eid(tile), e1 = eid(tile + stride);   // edge 0 past the last tile
+  const int i0 = a.dst[e0], j0 = a.col[e0];
+  int ni = a.dst[e1], nj = a.col[e1];
+  {
+    constexpr int NU = H * 2 / 16, NT = 64 * S::WAVES, N2 = H * NU / NT, N1 = 2 * H / NT;
+    static_assert(H * NU % NT == 0 && H <= NT && (2 * H <= NT || 2 * H % NT == 0), "whole rounds of the copy");
+    const uint4* src = reinterpret_cast<const uint4*>(P + a.L.w2p);
+    const uint4* w1l = reinterpret_cast<const uint4*>(P + a.L.w1l);
+    uint4 v2[N2], v1 = uint4{};
+#pragma unroll
+    for (int k = 0; k < N2; ++k) v2[k] = src[k * NT + tid];
+    static_assert(N1 <= 1, "W1 in one round");
+    const bool in1 = tid < 2 * H, inb = tid < H;
+    if (in1) v1 = w1l[tid];
+    const float bv1 = inb ? reinterpret_cast<const float*>(P + a.L.b1l)[tid] : 0.0f;
+    const float bv2 = inb ? reinterpret_cast<const float*>(P + a.L.b2)[tid] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < N2; ++k) {
+      const int U = k * NT + tid;
+      *reinterpret_cast<uint4*>(w2s + (U / NU) * S::W2B + (U % NU) * 16) = v2[k];
+    }
+    if (in1) reinterpret_cast<uint4*>(w1s)[tid] = v1;
+    if (inb) {
+      b1s[tid] = bv1;
+      b2s[tid] = bv2;
+    }
+  }
+  // Layer-1 A operand: W1[32 rt + l32][2 ks + hh] from the packed halves
+  // (neuron 32c + r sits in half (r/4)%2 at position 16c + 4(r/8) + r%4).
+  const int nks = attr_slots(a.dim, a.attr_mode) / 2;
+  const float* w1a = w1s + ((((l32 >> 2) & 1) * (H / 2) + 4 * (l32 >> 3) + (l32 & 3)) * 8 + hh);
+  // Loads run a tile ahead: a tile's attribute rows, and the ids of the tile
+  // after it, are issued before the stores of the tile in hand, so waiting
+  // for them never waits for those stores (loads and stores retire in one
+  // in-order count).  Lanes past E read edge 0 and store into the padding
+  // rows of the last tile.
   float ri[4], rj[4];
   auto load_rows = [&](int i, int j) {
     const float* pi = na + (size_t)i * rw;
@@ -686,23 +731,16 @@ __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void 
     ri[3] = rw == 4 ? pi[3] : 0.0f;
     rj[3] = rw == 4 ? pj[3] : 0.0f;
   };
-  {
-    const int64_t e0 = eid(tile);
-    load_rows(a.dst[e0], a.col[e0]);
-  }
-  int ni, nj;
-  {
-    const int64_t e1 = eid(tile + stride);
-    ni = a.dst[e1];
-    nj = a.col[e1];
-  }
+  load_rows(i0, j0);
+  __syncthreads();   // the weights are in LDS
+  if (tile >= ntiles) return;
 
   // The loop is re-entered with a tile's stores issued after the next tile's
   // loads.  The compiler's wait counts at the loop head take the smaller count
   // of its two ways in, so the way in from here issues as many stores after
   // those loads, into the spare mask rows past the last tile (never read).
   {
-    constexpr int NST = 2 * S::RT + 2 + (SPLIT ? S::SK + 1 : 0);
+    constexpr int NST = 2 * S::RT + (S::MW + 1) / 2 + (SPLIT ? 1 : 0);
     constexpr int RW = 2 * H / 32;   // mask words per edge
     uint32_t* sink = reinterpret_cast<uint32_t*>(a.zmask + (size_t)ntiles * 32 * RW * 4);
     // a lane-dependent row per store keeps them from merging into wider ones
@@ -740,9 +778,9 @@ __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void 
 
     // layer 1
     bf16x8 z1B[S::SK];
-    uint32_t m1[S::MW], m2[S::MW];
+    uint32_t m1[2 * S::MW], m2[2 * S::MW];   // 16-bit halves of the mask words
 #pragma unroll
-    for (int w = 0; w < S::MW; ++w) m1[w] = m2[w] = 0u;
+    for (int w = 0; w < 2 * S::MW; ++w) m1[w] = m2[w] = 0u;
 #pragma unroll
     for (int rt = 0; rt < S::RT; ++rt) {
       f32x16 C;
@@ -761,65 +799,61 @@ __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void 
       for (int j = 0; j < 2; ++j) {
         float zv[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int b = (2 * rt + j) * 8 + t;
-          zv[t] = relu_mask(C[8 * j + t], m1[b / 32], b % 32);
+        for (int t = 0; t < 8; ++t) zv[t] = C[8 * j + t];
+        z1B[2 * rt + j] = relu_pack_mask(zv, m1[rt], 8 * j);
+      }
+    }
+    // layer 2, two 32-row tiles of outputs (128 bytes of an edge's z row) at a time
+#pragma unroll
+    for (int kp = 0; kp < S::RT; kp += 2) {
+      uint4 f[2][2];   // [tile][half of its rows]
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int kt = kp + k;
+        f32x16 C;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 b = *reinterpret_cast<const f32x4*>(b2s + kt * 32 + 8 * q + 4 * hh);
+          C[4 * q] = b[0]; C[4 * q + 1] = b[1]; C[4 * q + 2] = b[2]; C[4 * q + 3] = b[3];
         }
-        z1B[2 * rt + j] = pack_frag<__bf16>(zv);
-      }
-      // fold the tile's mask bits into their words here rather than at the store
 #pragma unroll
-      for (int w = 0; w < S::MW; ++w) asm("" : "+v"(m1[w]));
-    }
-    if constexpr (SPLIT) {
-      if (a.z1E) {   // without z1 rows the backward recomputes z1 from the split attributes
-#pragma unroll
-        for (int s = 0; s < S::SK; ++s)
-          *reinterpret_cast<bf16x8*>(a.z1E + ((size_t)e * H + s * 16 + hh * 8) * 2) = z1B[s];
-      }
-    }
-
-    // layer 2, one 32-row tile of outputs at a time
-#pragma unroll
-    for (int kt = 0; kt < S::RT; ++kt) {
-      f32x16 C;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 b = *reinterpret_cast<const f32x4*>(b2s + kt * 32 + 8 * q + 4 * hh);
-        C[4 * q] = b[0]; C[4 * q + 1] = b[1]; C[4 * q + 2] = b[2]; C[4 * q + 3] = b[3];
-      }
-#pragma unroll
-      for (int s = 0; s < S::SK; ++s) {
-        const bf16x8 A = *reinterpret_cast<const bf16x8*>(w2s + (kt * 32 + l32) * S::W2B + (s * 16 + hh * 8) * 2);
-        C = M::mma(A, z1B[s], C);
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        float zv[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int b = 16 * kt + 8 * j + t;
-          zv[t] = relu_mask(C[8 * j + t], m2[b / 32], b % 32);
+        for (int s = 0; s < S::SK; ++s) {
+          const bf16x8 A = *reinterpret_cast<const bf16x8*>(w2s + (kt * 32 + l32) * S::W2B + (s * 16 + hh * 8) * 2);
+          C = M::mma(A, z1B[s], C);
         }
-        *reinterpret_cast<bf16x8*>(a.zE + ((size_t)e * H + (2 * kt + j) * 16 + hh * 8) * 2) =
-            pack_frag<__bf16>(zv);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          float zv[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) zv[t] = C[8 * j + t];
+          f[k][j] = __builtin_bit_cast(uint4, relu_pack_mask(zv, m2[kt], 8 * j));
+        }
       }
-#pragma unroll
-      for (int w = 0; w < S::MW; ++w) asm("" : "+v"(m2[w]));
+      store_z_lines(f, a.zE + (size_t)tile * 32 * H * 2 + kp * 64, H * 2);
     }
-    uint32_t* mb = reinterpret_cast<uint32_t*>(a.zmask + (size_t)e * (2 * H / 8));
+    // the row is z1's words of lane halves 0 and 1, then z's: the halves change
+    // places so that half 0 holds all of z1's and half 1 all of z's
+    uint32_t mw[2 * S::MW];
 #pragma unroll
-    for (int w = 0; w < S::MW; ++w) mb[hh * S::MW + w] = m1[w];
+    for (int w = 0; w < S::MW; ++w) {
+      const auto r = __builtin_amdgcn_permlane32_swap(m1[2 * w] | m1[2 * w + 1] << 16, m2[2 * w] | m2[2 * w + 1] << 16,
+                                                      false, false);
+      mw[w] = r[0];
+      mw[S::MW + w] = r[1];
+    }
+    uint32_t* mb = reinterpret_cast<uint32_t*>(a.zmask + (size_t)e * (2 * H / 8)) + hh * 2 * S::MW;
+    if constexpr (S::MW == 1) *reinterpret_cast<uint2*>(mb) = make_uint2(mw[0], mw[1]);
 #pragma unroll
-    for (int w = 0; w < S::MW; ++w) mb[2 * S::MW + hh * S::MW + w] = m2[w];
+    for (int w = 0; w + 4 <= 2 * S::MW; w += 4)
+      *reinterpret_cast<uint4*>(mb + w) = make_uint4(mw[w], mw[w + 1], mw[w + 2], mw[w + 3]);
   }
 }
 
 template <int H>
 dsmp_status launch_edge_mlp(dsmp_handle* h, const EdgeArgs& a) {
   using S = MlpShape<H>;
-  DSMP_CHECK(h, a.zE != nullptr && a.zmask != nullptr && (a.z1E == nullptr || a.xE != nullptr),
-             DSMP_INVALID_ARG, "kernel MLP: z and the mask bits are always stored, z1 only with x");
+  DSMP_CHECK(h, a.zE != nullptr && a.zmask != nullptr && a.z1E == nullptr, DSMP_INVALID_ARG,
+             "kernel MLP: z and the mask bits are always stored, z1 never");
   auto kern = a.xE ? k_edge_mlp<H, true> : k_edge_mlp<H, false>;
   DSMP_HIP(h, hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS));
