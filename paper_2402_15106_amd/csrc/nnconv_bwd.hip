@@ -680,7 +680,7 @@ __global__ __launch_bounds__(256, (DL <= 64 && H2 * sizeof(T) <= 256) ? 3 : 1) v
 // One pass over 32-edge tiles computes dz = U_i h_j, the masked da2,
 // dz1 = W2^T da2 and da1 (as k_bwd_dz_agg does), and folds the per-edge
 // weight gradients straight into per-workgroup sums, so da2 and da1 never go
-// to HBM.  A workgroup takes blocks of 16 destinations; a tile is 32
+// to HBM.  A workgroup takes blocks of nb destinations; a tile is 32
 // consecutive edges of the block's rows, so it may cross destinations: dz
 // runs once per destination in the tile, with the B operand restricted to
 // that destination's lanes (every tile is full but the block's last, where a
@@ -704,6 +704,7 @@ __global__ __launch_bounds__(256, (DL <= 64 && H2 * sizeof(T) <= 256) ? 3 : 1) v
 // while the products run; the barriers order LDS traffic only.
 // Partial sums go to slot blockIdx.x of the dW2/db2 and dW1/db1 partial
 // buffers, summed later in a fixed order.
+constexpr int EG_NB = 60;   // row pointers of a block fit one wave
 struct EdgeGradArgs {
   DzArgs dz;
   const float* node_attr;
@@ -711,6 +712,7 @@ struct EdgeGradArgs {
   unsigned char* da1_out;   // [E][h1] bf16 permuted order, or null (needed for the attribute gradient)
   float* p_w2;              // [gridDim.x][h2*h1 + h2]
   float* p_w1;              // [gridDim.x][h1*de + h1]
+  int nb;                   // destinations per block, 1 .. EG_NB
 };
 
 template <int DL, int H1, int H2>
@@ -772,7 +774,7 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
   stage_wait();
   __syncthreads();   // W2^T and the layer-1 weights are in LDS
 
-  __shared__ int rps[DZ_NB + 1];
+  __shared__ int rps[EG_NB + 1];
   __shared__ int slot_cnt[4];
   unsigned char* myslot = slots + pr * G::SLOT;
   // A operands of the z1 product, built each round from the fp32 weights in
@@ -1099,10 +1101,10 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
     lds_barrier();   // slots are free for the next round
   };
 
-  const int64_t nblk = (a.n_dst + DZ_NB - 1) / DZ_NB;
+  const int64_t nblk = (a.n_dst + g.nb - 1) / g.nb;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    d0 = (int)(blk * DZ_NB);
-    nd = (int)(a.n_dst - d0 < DZ_NB ? a.n_dst - d0 : DZ_NB);
+    d0 = (int)(blk * g.nb);
+    nd = (int)(a.n_dst - d0 < g.nb ? a.n_dst - d0 : g.nb);
     if (wv == 0 && lane <= nd) rps[lane] = a.row_ptr[d0 + lane];
     lds_barrier();
     ntile = (rps[nd] - rps[0] + 31) / 32;
@@ -2969,10 +2971,19 @@ dsmp_status run_edge_grads_fused(dsmp_handle* h, const EdgeGradArgs& eg, int cap
   if (st != DSMP_OK) return st;
   int per_cu = 0;
   DSMP_HIP(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kf, G::NT, G::LDS));
-  int64_t grid = std::min<int64_t>((dz.n_dst + DZ_NB - 1) / DZ_NB, (int64_t)h->n_cu * std::max(per_cu, 1));
-  grid = std::max<int64_t>(1, std::min<int64_t>(grid, cap));
+  // Blocks as even as they come: every workgroup of the chip gets one of up to
+  // EG_NB destinations, or the same number of them.  Each block starts with three
+  // loads that wait for one another and ends with a part-filled round; blocks of
+  // 16 gave 900 destinations to 57 workgroups: 27 -> 17 us there, 2,048 of degree
+  // 13 and 21 29 -> 23 and 35 -> 25, 40,000 of degree 27 311 -> 301, and at d = 32
+  // 40,000 of degree 23 168 -> 159.
+  const int64_t slots = std::max<int64_t>(1, std::min<int64_t>((int64_t)h->n_cu * std::max(per_cu, 1), cap));
+  const int64_t rounds = std::max<int64_t>(1, ceil_div(dz.n_dst, slots * EG_NB));
+  EdgeGradArgs ea = eg;
+  ea.nb = (int)std::max<int64_t>(1, ceil_div(dz.n_dst, slots * rounds));
+  const int64_t grid = std::min<int64_t>(ceil_div(dz.n_dst, ea.nb), slots);
   ProfScope prof(h, DSMP_K_DZ);
-  hipLaunchKernelGGL(kf, dim3((unsigned)grid), dim3(G::NT), G::LDS, s, eg);
+  hipLaunchKernelGGL(kf, dim3((unsigned)grid), dim3(G::NT), G::LDS, s, ea);
   DSMP_LAUNCHED(h, "fused edge gradients");
   *nchunk = (int)grid;
   return DSMP_OK;
