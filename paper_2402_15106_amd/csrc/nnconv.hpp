@@ -351,6 +351,69 @@ __device__ __forceinline__ bf16x8 relu_pack_mask(const float* v, uint32_t& half,
   return f;
 }
 
+// Pieces of 32 rows into whole cache lines.  f[k][j] of lane (i, h) is the 16
+// bytes at 64 k + 32 j + 16 h of row i's 128 bytes; x[r][q] is then the 16 bytes
+// at line_piece(lane) of row 16 r + 8 q + lane % 8.  Rows 0..15 and 16..31 change
+// places between the two j (lanes 16 apart), then rows 8 apart between the two k.
+// As they stand a store would touch 32 lines for 32 bytes each.
+__device__ __forceinline__ void rows_to_lines(const uint4 (&f)[2][2], uint4 (&x)[2][2]) {
+  const uint32_t(*w)[2][4] = reinterpret_cast<const uint32_t(*)[2][4]>(&f[0][0]);
+  uint32_t(*o)[2][4] = reinterpret_cast<uint32_t(*)[2][4]>(&x[0][0]);
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    uint32_t v[2][2];   // [k][rows 16 * .]
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const auto r = __builtin_amdgcn_permlane16_swap(w[k][0][d], w[k][1][d], false, false);
+      v[k][0] = r[0];
+      v[k][1] = r[1];
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {   // row_ror:8, into lanes 8..15 and 0..7 of each row of 16
+      o[r][0][d] = __builtin_amdgcn_update_dpp(v[0][r], v[1][r], 0x128, 0xf, 0xc, false);
+      o[r][1][d] = __builtin_amdgcn_update_dpp(v[1][r], v[0][r], 0x128, 0xf, 0x3, false);
+    }
+  }
+}
+
+__device__ __forceinline__ int line_piece(int lane) {
+  return ((lane >> 3) & 1) * 64 + ((lane >> 4) & 1) * 32 + (lane >> 5) * 16;
+}
+
+// A 32 x 32 accumulator tile (lane = row, register r = column 8 (r / 4) + 4 h +
+// r % 4) as bf16 in 64-byte row pieces: x[r] is the 16 bytes at half_piece(lane)
+// of row 16 r + lane % 16.
+__device__ __forceinline__ void tile_to_lines(const f32x16& acc, uint4 (&x)[2]) {
+  uint32_t p[4][2];   // column groups of 8, two words each
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const bf16x2 b = __builtin_convertvector((f32x2){acc[4 * g + 2 * i], acc[4 * g + 2 * i + 1]}, bf16x2);
+      p[g][i] = __builtin_bit_cast(uint32_t, b);
+    }
+  uint32_t f[2][4];   // 16 bytes at 32 j + 16 h of the lane's row
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const auto r = __builtin_amdgcn_permlane32_swap(p[2 * j][i], p[2 * j + 1][i], false, false);
+      f[j][i] = r[0];
+      f[j][2 + i] = r[1];
+    }
+  uint32_t o[2][4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const auto r = __builtin_amdgcn_permlane16_swap(f[0][d], f[1][d], false, false);
+    o[0][d] = r[0];
+    o[1][d] = r[1];
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r) x[r] = make_uint4(o[r][0], o[r][1], o[r][2], o[r][3]);
+}
+
+__device__ __forceinline__ int half_piece(int lane) { return ((lane >> 4) & 1) * 32 + (lane >> 5) * 16; }
+
 // p[0] + p[stride] + ... + p[(n-1) stride], added in index order starting
 // from +0 (the same bits as the plain loop), with the loads issued eight at a
 // time ahead of their additions instead of one load-wait-add per term.

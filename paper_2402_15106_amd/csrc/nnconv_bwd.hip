@@ -2237,7 +2237,8 @@ __device__ __forceinline__ bf16x8 lds_frag_ut(const unsigned char* X, int P0, in
 // bias fragments of b3 are loaded once.  While destination i is multiplied,
 // the next destination's U and the operands of the wave's first item of it
 // (its z rows and g) are already on their way, so the loop waits on one
-// round of loads per destination.
+// round of loads per destination.  Bound by memory: at 8,192 destinations of 39
+// edges, d = 64, 257 MB in 53 us (60 with m_e stored in 8-byte pieces).
 template <int DL, int H2>
 __global__ __launch_bounds__(256) void k_dh_u(DhuArgs a) {
   using S = DhuShape<DL, H2>;
@@ -2263,22 +2264,18 @@ __global__ __launch_bounds__(256) void k_dh_u(DhuArgs a) {
   };
   auto item = [&](const unsigned char* Xb, int64_t pa, int64_t pb, int et, const bf16x8 (&zb)[SK2],
                   const bf16x8 (&gb)[SKD]) {
-    const int64_t e = pa + (int64_t)et * 32 + l32;
     f32x16 acc = f32x16{};
     // bias row: sum_q b3[p*d+q] g_i[q], the same for every edge column
 #pragma unroll
     for (int sf = 0; sf < SKD; ++sf) acc = M::mma(ba[sf], gb[sf], acc);
 #pragma unroll
     for (int s2 = 0; s2 < SK2; ++s2) acc = M::mma(lds_frag_ut<DL>(Xb, 16 * s2, 32 * pt), zb[s2], acc);
-    if (e < pb) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const bf16x2 lo = __builtin_convertvector((f32x2){acc[4 * g], acc[4 * g + 1]}, bf16x2);
-        const bf16x2 hi = __builtin_convertvector((f32x2){acc[4 * g + 2], acc[4 * g + 3]}, bf16x2);
-        *reinterpret_cast<uint2*>(a.mE + ((size_t)e * DL + 32 * pt + 8 * g + 4 * hh) * 2) =
-            make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-      }
-    }
+    uint4 x[2];
+    tile_to_lines(acc, x);
+    const int64_t er = pa + (int64_t)et * 32 + (lane & 15);
+    unsigned char* mp = a.mE + ((size_t)er * DL + 32 * pt) * 2 + half_piece(lane);
+    if (er < pb) *reinterpret_cast<uint4*>(mp) = x[0];
+    if (er + 16 < pb) *reinterpret_cast<uint4*>(mp + 16 * DL * 2) = x[1];
   };
   int64_t i = blockIdx.x;
   if (i >= a.n_dst) return;
@@ -2377,8 +2374,11 @@ __global__ __launch_bounds__(256) void k_dh_gather(int64_t n_src, int64_t n_dst,
 // The two per-edge products that read U_i, dz_e = U_i h_j and
 // m_e = U~_i^T z~_e, in one pass over each destination's edges (bf16 layers
 // whose kernel-MLP gradients are not fused), so that U is read from HBM once for
-// both: at d = 64, 100,000 destinations of 10.8 edges, 530 us (1.64 GB of U,
-// 0.8 GB of rows), where the fused pass and k_dh_u take 472 and 477 us.  U_i and g_i are copied to LDS as they stand (direct
+// both: at d = 64, 100,000 destinations of 10.8 edges, 475 us for 1.64 GB of U
+// and 0.85 GB of rows (5.2 TB/s), where the fused pass and k_dh_u take 472 and
+// 427 us.  m_e and da2 leave in 64- and 128-byte pieces of their rows: 8- and
+// 32-byte ones took 529 us (5,750 against 5,650 at 262,144 destinations, d = 128).
+// U_i and g_i are copied to LDS as they stand (direct
 // global-to-LDS loads, double-buffered over destinations).  Of the d / 32
 // waves, wave w takes, for every 32-edge tile of the destination, the two
 // 32-neuron tiles 2w, 2w + 1 of dz (A = U_i fragments read from LDS as
@@ -2437,7 +2437,6 @@ __global__ __launch_bounds__(2 * DL, DL == 64 ? 2 : 1) void k_dz_dh_u(DzDhuArgs 
     o.mw = valid ? w : 0u;
   };
   auto item = [&](const unsigned char* Xb, int64_t pa, int64_t pb, int et, const Ops& o) {
-    const int64_t e = pa + (int64_t)et * 32 + l32;
     f32x16 acc = f32x16{};
     // m_e: the bias row sum_q b3[p*d+q] g_i[q], then the z~ . U_i terms
 #pragma unroll
@@ -2455,26 +2454,34 @@ __global__ __launch_bounds__(2 * DL, DL == 64 ? 2 : 1) void k_dz_dh_u(DzDhuArgs 
         dz[kk] = M::mma(*reinterpret_cast<const bf16x8*>(Xb + (((KTW * wv + kk) * SKD + s) * 64 + lane) * 16),
                         o.h[s], dz[kk]);
     }
-    // The tile's only memory operations after the products: eight stores
-    // (four of m_e, four of da2).  The next step's wait count relies on it.
-    if (e < pb) {
+    // The tile's only memory operations after the products: one store per 16
+    // rows of m_e and per 8 rows of da2 that it has (n_stores), in 64- and 128-byte
+    // pieces.  The next step's wait count relies on it.
+    const int cnt = pb - pa - (int64_t)et * 32 < 32 ? (int)(pb - pa - (int64_t)et * 32) : 32;
+    const int64_t e0 = pa + (int64_t)et * 32;
+    uint4 mx[2], f[2][2], x[2][2];
+    tile_to_lines(acc, mx);
+    unsigned char* mp = d.mE + ((size_t)(e0 + (lane & 15)) * DL + 32 * wv) * 2 + half_piece(lane);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const bf16x2 lo = __builtin_convertvector((f32x2){acc[4 * g], acc[4 * g + 1]}, bf16x2);
-        const bf16x2 hi = __builtin_convertvector((f32x2){acc[4 * g + 2], acc[4 * g + 3]}, bf16x2);
-        *reinterpret_cast<uint2*>(d.mE + ((size_t)e * DL + 32 * wv + 8 * g + 4 * hh) * 2) =
-            make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-      }
-      // da2 positions 16 s + 8 hh + u, s = 4w + sl, hold dz register 8 (sl % 2) + u of tile sl / 2
+    for (int r = 0; r < 2; ++r)
+      if (cnt > 16 * r && 16 * r + (lane & 15) < cnt) *reinterpret_cast<uint4*>(mp + 16 * r * DL * 2) = mx[r];
+    // da2 positions 16 s + 8 hh + u, s = 4w + sl, hold dz register 8 (sl % 2) + u of tile sl / 2
 #pragma unroll
-      for (int sl = 0; sl < 4; ++sl) {
-        float v[8];
+    for (int sl = 0; sl < 4; ++sl) {
+      float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = keep_if_bit(dz[sl / 2][8 * (sl % 2) + u], o.mw, 8 * sl + u);
-        *reinterpret_cast<bf16x8*>(a.da2E + ((size_t)e * H2 + 16 * (4 * wv + sl) + 8 * hh) * 2) =
-            pack_frag<__bf16>(v);
-      }
+      for (int u = 0; u < 8; ++u) v[u] = keep_if_bit(dz[sl / 2][8 * (sl % 2) + u], o.mw, 8 * sl + u);
+      f[sl / 2][sl % 2] = __builtin_bit_cast(uint4, pack_frag<__bf16>(v));
     }
+    rows_to_lines(f, x);
+    unsigned char* dp = a.da2E + (size_t)(e0 + (lane & 7)) * H2 * 2 + 128 * wv + line_piece(lane);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int r8 = 16 * r + 8 * q;
+        if (cnt > r8 && r8 + (lane & 7) < cnt) *reinterpret_cast<uint4*>(dp + r8 * H2 * 2) = x[r][q];
+      }
   };
   const int64_t i0 = blockIdx.x, G = gridDim.x;
   if (i0 >= d.n_dst) return;
@@ -2517,12 +2524,16 @@ __global__ __launch_bounds__(2 * DL, DL == 64 ? 2 : 1) void k_dz_dh_u(DzDhuArgs 
   // operands in cur; the next destination's copies go to Xn, its operands to
   // nxt.  The loop alternates the two (buffers, operand sets) in code, so no
   // buffer is chosen at run time and no operand set is copied.
-  int prev_net = 0;   // edge tiles of the previous destination (its stores follow the copies)
+  int prev = 0;   // edges of the previous destination (its stores follow the copies)
   auto step = [&](int64_t i, const unsigned char* Xc, unsigned char* Xn, const Ops& cur, Ops& nxt) {
     // the copies of U_i and g_i: after them the previous step issued only its
-    // tile's eight stores when it had one tile, which may stay in flight
-    if (prev_net == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
-    else stage_wait();
+    // tile's stores when it had one tile, which may stay in flight: one per 16
+    // and one per 8 edges
+    if (prev == 0 || prev > 32) stage_wait();
+    else if (prev > 24) __builtin_amdgcn_s_waitcnt(vmcnt_imm(6));
+    else if (prev > 16) __builtin_amdgcn_s_waitcnt(vmcnt_imm(5));
+    else if (prev > 8) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(2));
     lds_sync();   // U_i, g_i in Xc; every wave is done with Xn (LDS only: stores stay in flight)
     int64_t pa3, pb3;
     rows(i + 3 * G, pa3, pb3);
@@ -2537,7 +2548,7 @@ __global__ __launch_bounds__(2 * DL, DL == 64 ? 2 : 1) void k_dz_dh_u(DzDhuArgs 
     }
     asm volatile("" ::: "memory");   // the copies stay ahead of the tile's stores
     __builtin_amdgcn_sched_barrier(0);
-    const int net = (int)((pb - pa + 31) / 32);
+    const int prev_edges = (int)(pb - pa), net = (prev_edges + 31) / 32;
     if (net > 0) item(Xc, pa, pb, 0, cur);
     for (int et = 1; et < net; ++et) {   // destinations of more than 32 edges
       const int64_t e = pa + (int64_t)et * 32 + l32;
@@ -2551,7 +2562,7 @@ __global__ __launch_bounds__(2 * DL, DL == 64 ? 2 : 1) void k_dz_dh_u(DzDhuArgs 
     pa1 = pa2; pb1 = pb2;
     pa2 = pa3; pb2 = pb3;
     c1 = c2;
-    prev_net = net;
+    prev = prev_edges;
   };
   for (int64_t i = i0;;) {
     step(i, XA, XB, opsA, opsB);

@@ -605,8 +605,8 @@ __global__ __launch_bounds__(256) void k_fwd_node_m(NodeArgs a) {
 // Layers 1 and 2 of the kernel network K_phi (eq. (1)) for every edge, the
 // pass the aggregate form runs ahead of its per-destination sums (bf16
 // layers):  z1 = ReLU(W1 x + b1),  z = ReLU(W2 z1 + b2),  with the ReLU mask
-// bits of both, and z1 and the split attributes when the backward reads them
-// back.  Both layers are matrix-core products over a 32-edge tile:
+// bits of both, and the split attributes when the backward reads them back.
+// Both layers are matrix-core products over a 32-edge tile:
 //  * layer 1 in fp32, 32x32x2 steps over the attribute slots that can be
 //    nonzero (two per step), with the bias as the accumulator's initial
 //    value: any fp32 evaluation order of the pre-activation is within the
@@ -619,6 +619,12 @@ __global__ __launch_bounds__(256) void k_fwd_node_m(NodeArgs a) {
 // each half of a 32-row tile's accumulators is one B fragment as it stands,
 // and the mask bits come out in the stored format.  Workgroups are
 // persistent; each wave takes every (grid * waves)-th tile.
+//
+// Bound by its stores (288 bytes per edge at H = 128; with a third of the vector
+// instructions removed and the stores as they were nothing changed): z leaves in
+// whole cache lines, the mask bits 16 bytes a lane, where 32- and 8-byte pieces
+// of a row took, at 1,079,000 edges, 117 us against 95 now (3.6 TB/s); 321,000
+// edges 38 and 32 us, 262,144 destinations at H = 256 1,235 and 1,150 us.
 template <int H>
 struct MlpShape {
   static constexpr int WAVES = H <= 128 ? 4 : 8;    // waves per workgroup
@@ -628,38 +634,6 @@ struct MlpShape {
   static constexpr int LDS = H * W2B + 10 * H * 4;  // W2; W1 and b1 (packed halves); b2
   static constexpr int MW = H / 64;                 // mask words per lane half and layer
 };
-
-// Stores 128 bytes of each of 32 rows as whole cache lines: f[k][j] of lane (i,
-// h) is the 16 bytes at 64 k + 32 j + 16 h of row i.  Rows 0..15 and 16..31
-// change places between the two j (lanes 16 apart), then rows 8 apart between
-// the two k, so that eight lanes hold the eight pieces of a row; as they stand
-// a store would touch 32 lines for 32 bytes each.
-__device__ __forceinline__ void store_z_lines(uint4 (&f)[2][2], unsigned char* base, int pitch) {
-  uint32_t(*w)[2][4] = reinterpret_cast<uint32_t(*)[2][4]>(&f[0][0]);
-  const int lane = threadIdx.x & 63;
-  uint32_t x[2][2][4];   // [rows 16 * .][rows 8 * .]
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    uint32_t v[2][2];   // [tile][rows 16 * .]
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const auto r = __builtin_amdgcn_permlane16_swap(w[k][0][d], w[k][1][d], false, false);
-      v[k][0] = r[0];
-      v[k][1] = r[1];
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {   // row_ror:8, into lanes 8..15 and 0..7 of each row of 16
-      x[r][0][d] = __builtin_amdgcn_update_dpp(v[0][r], v[1][r], 0x128, 0xf, 0xc, false);
-      x[r][1][d] = __builtin_amdgcn_update_dpp(v[1][r], v[0][r], 0x128, 0xf, 0x3, false);
-    }
-  }
-  unsigned char* p = base + (lane & 7) * pitch + ((lane >> 3) & 1) * 64 + ((lane >> 4) & 1) * 32 + (lane >> 5) * 16;
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-      *reinterpret_cast<uint4*>(p + (16 * r + 8 * q) * pitch) = make_uint4(x[r][q][0], x[r][q][1], x[r][q][2], x[r][q][3]);
-}
 
 template <int H, bool SPLIT>
 __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void k_edge_mlp(EdgeArgs a,
@@ -684,8 +658,8 @@ __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void 
   };
   // W2, W1 and the biases to LDS, once per workgroup: every load goes out
   // before the first is waited for, the ids of the wave's first two tiles ahead
-  // of them (one load and wait per 16 bytes and the ids after the copy took half
-  // the time of a launch with one tile per wave: 18.4 us for 39,000 edges, ...)
+  // of them.  One load and wait per round of the copy, and the ids after it, cost
+  // 1.3 us of 20 for 100,000 edges.
   const int64_t e0 = eid(tile), e1 = eid(tile + stride);   // edge 0 past the last tile
   const int i0 = a.dst[e0], j0 = a.col[e0];
   int ni = a.dst[e1], nj = a.col[e1];
@@ -829,7 +803,13 @@ __global__ __launch_bounds__(64 * MlpShape<H>::WAVES, MlpShape<H>::PER_CU) void 
           f[k][j] = __builtin_bit_cast(uint4, relu_pack_mask(zv, m2[kt], 8 * j));
         }
       }
-      store_z_lines(f, a.zE + (size_t)tile * 32 * H * 2 + kp * 64, H * 2);
+      uint4 x[2][2];
+      rows_to_lines(f, x);
+      unsigned char* zp = a.zE + (size_t)tile * 32 * H * 2 + kp * 64 + (lane & 7) * H * 2 + line_piece(lane);
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) *reinterpret_cast<uint4*>(zp + (16 * r + 8 * q) * H * 2) = x[r][q];
     }
     // the row is z1's words of lane halves 0 and 1, then z's: the halves change
     // places so that half 0 holds all of z1's and half 1 all of z's
