@@ -1279,14 +1279,18 @@ struct TStage {
   __device__ __forceinline__ void fetch(const unsigned char* __restrict__ src, int64_t eb, int64_t e_end) {
 #pragma unroll
     for (int x = 0; x < UPT; ++x) {
-      const int u = (int)threadIdx.x + x * 256, eq = u % EQ, kg = u / EQ;
+      const int u = (int)threadIdx.x + x * 256 < NU ? (int)threadIdx.x + x * 256 : NU - 1, eq = u % EQ, kg = u / EQ;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t e = eb + 4 * eq + i;
-        v[x][i] = (u < NU && e < e_end) ? *reinterpret_cast<const uint4*>(src + ((size_t)e * W) * ESZ + kg * 16)
-                                       : make_uint4(0, 0, 0, 0);
+      for (int i = 0; i < 4; ++i) {   // rows past the end re-read the last one: a load under a condition is waited for
+        const int64_t e = eb + 4 * eq + i < e_end ? eb + 4 * eq + i : e_end - 1;
+        v[x][i] = *reinterpret_cast<const uint4*>(src + ((size_t)e * W) * ESZ + kg * 16);
       }
     }
+#pragma unroll
+    for (int x = 0; x < UPT; ++x)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (eb + 4 * (((int)threadIdx.x + x * 256) % EQ) + i >= e_end) v[x][i] = make_uint4(0, 0, 0, 0);
   }
   template <int ROWB>
   __device__ __forceinline__ void store(unsigned char* __restrict__ dstl) const {
