@@ -384,7 +384,9 @@ __global__ __launch_bounds__(1024) void k_sel_count(int64_t M, uint64_t seed, co
   if (threadIdx.x == 0) cnt[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(1024) void k_sel_write(int64_t M, uint64_t seed, const unsigned long long* threshold,
+// At most s are written, whatever the threshold and the offsets are.
+__global__ __launch_bounds__(1024) void k_sel_write(int64_t M, uint32_t s, uint64_t seed,
+                                                    const unsigned long long* threshold,
                                                     const uint32_t* __restrict__ off,
                                                     int32_t* __restrict__ out) {
   __shared__ uint32_t sh[32];
@@ -392,7 +394,9 @@ __global__ __launch_bounds__(1024) void k_sel_write(int64_t M, uint64_t seed, co
   uint32_t f = (i < M && splitmix64(seed, (uint64_t)i) <= *threshold) ? 1u : 0u;
   uint32_t tot;
   uint32_t ex = block_exclusive_scan_1024(f, sh, &tot);
-  if (f) out[off[blockIdx.x] + ex] = (int32_t)i;
+  if (!f) return;
+  const uint32_t at = off[blockIdx.x] + ex;
+  if (at < s) out[at] = (int32_t)i;
 }
 
 // ---- one workgroup, and the middle form
@@ -481,13 +485,15 @@ __global__ __launch_bounds__(1024) void k_mid_init(SelMid* st, uint32_t* hist) {
 }
 
 // Whether this workgroup is the last of the grid to get here.  What the
-// others wrote before it is then visible to agent-scope loads.  One thread
-// fences for its workgroup, after the barrier has completed the workgroup's
-// writes (a fence by every thread is a write-back of the L2 by every wave:
-// k_mid_list at 764,077 candidates takes 182 us with it and 746 workgroups, 31
-// with one fence each, 16 with at most SEL_GRID workgroups).
+// others wrote before it is then visible to agent-scope loads.  The barrier
+// alone does not complete the workgroup's writes (it compiles to a wait for LDS
+// operations and s_barrier), so every wave first waits for its own; one thread
+// then fences for all of them (a fence by every thread is a write-back of the
+// L2 by every wave: k_mid_list at 764,077 candidates takes 182 us with it and 746
+// workgroups, 31 with one fence each, 16 with at most SEL_GRID workgroups).
 __device__ __forceinline__ bool last_block(unsigned* counter) {
   __shared__ unsigned last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
@@ -631,7 +637,8 @@ dsmp_status sample_run(dsmp_handle* h, int64_t M, int64_t s, uint64_t seed, int3
     hipLaunchKernelGGL(k_mid_hist, dim3(std::min(ceil_div(M, 4096), (unsigned)SEL_GRID)), dim3(1024), 0, h->stream, M, (uint32_t)s,
                        seed, ms, mh);
     hipLaunchKernelGGL(k_mid_list, dim3(std::min(nb, SEL_GRID)), dim3(1024), 0, h->stream, M, seed, ms, list, cnt, nb);
-    hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, seed, &ms->threshold, cnt, idx_out);
+    hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, (uint32_t)s, seed, &ms->threshold, cnt,
+                       idx_out);
     DSMP_LAUNCHED(h, "sample");
     return DSMP_OK;
   }
@@ -645,7 +652,8 @@ dsmp_status sample_run(dsmp_handle* h, int64_t M, int64_t s, uint64_t seed, int3
   }
   hipLaunchKernelGGL(k_sel_count, dim3(nb), dim3(1024), 0, h->stream, M, seed, st, cnt);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, h->stream, cnt, nb);
-  hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, seed, &st->prefix, cnt, idx_out);
+  hipLaunchKernelGGL(k_sel_write, dim3(nb), dim3(1024), 0, h->stream, M, (uint32_t)s, seed, &st->prefix, cnt,
+                       idx_out);
   DSMP_LAUNCHED(h, "sample");
   return DSMP_OK;
 }

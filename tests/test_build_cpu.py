@@ -1,6 +1,11 @@
-"""The build's guard against kernels that use scratch memory (no GPU)."""
+"""Checks of the compiled device code, no GPU: the build's guard against kernels
+that use scratch memory, and the waits ahead of a hand-off between workgroups."""
 import os
+import re
+import subprocess
 import sys
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
@@ -19,3 +24,28 @@ a.hip:9:1: remark:     ScratchSize [bytes/lane]: 240 [-Rpass-analysis=kernel-res
 def test_scratch_kernels_names_only_the_spilling_kernel():
     assert build.scratch_kernels(REMARKS) == ["k_two (240 bytes/lane)"]
     assert build.scratch_kernels("") == []
+
+
+@pytest.fixture(scope="module")
+def core_asm(tmp_path_factory):
+    """core.hip's gfx950 assembly, with the library's own flags."""
+    out = str(tmp_path_factory.mktemp("asm") / "core.s")
+    cmd = [build._hipcc()] + build.COMMON + ["--offload-device-only", "-S", os.path.join(build.CSRC, "core.hip"), "-o", out]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=300)
+    return open(out).read()
+
+
+@pytest.mark.parametrize("kernel", ["k_mid_hist", "k_mid_list"])
+def test_every_wave_waits_for_its_writes_before_the_hand_off(core_asm, kernel):
+    """One thread fences for its workgroup and counts it as done.  The barrier
+    ahead of that fence orders LDS only, so each wave's own global writes have to
+    be waited for before it."""
+    body = re.search(r"^_ZN\S*%s\S*:.*?s_endpgm" % kernel, core_asm, re.M | re.S).group(0)
+    code = [l.split(";")[0].strip() for l in body.splitlines()]
+    fence = next(i for i, l in enumerate(code) if l.startswith("buffer_wbl2"))
+    barrier = max(i for i, l in enumerate(code[:fence]) if l == "s_barrier")
+    ops = [i for i, l in enumerate(code[:barrier]) if l.startswith(("global_", "flat_", "buffer_"))]
+    waits = [i for i, l in enumerate(code[:barrier]) if l.startswith("s_waitcnt") and "vmcnt(0)" in l]
+    assert ops and waits and waits[-1] > ops[-1], (kernel, code[ops[-1]], code[barrier])
+    # and it is not skipped: no branch target between the wait and the barrier
+    assert not any(l.endswith(":") for l in code[waits[-1]:barrier])
