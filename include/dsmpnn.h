@@ -22,6 +22,11 @@
  *     enqueued (argument errors are found on the host before any launch),
  *     except where a call states otherwise; dsmp_last_error(h) then holds a
  *     message.  The library never aborts the process.
+ *   - Host threads: calls on different handles are independent.  Two threads
+ *     may also make calls on one handle at once, each with buffers and a
+ *     workspace of its own; all of it goes to the handle's one stream.  A
+ *     handle's settings (stream, edge algorithm, kernel timing) are then left
+ *     alone, and dsmp_last_error gives the message of either thread's failure.
  *   - Integer index arrays are int32 (sizes beyond 2^31-1 edges or nodes
  *     are rejected with DSMP_UNSUPPORTED).
  *   - Results are deterministic: the same inputs give bitwise-identical

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <mutex>
 #include <string>
 #include <vector>
 #include <algorithm>
@@ -19,10 +20,15 @@ struct dsmp_handle {
   int n_cu = 256;      // compute units of the device (sizes persistent grids)
   void* sample_scratch = nullptr;   // device address of the allocation-free sampling scratch
   // READBACK_BYTES of pinned host memory (allocated at creation) that kernels
-  // write small results to for the calls that synchronise, and its device address
+  // write small results to for the calls that synchronise, and its device
+  // address.  A call holds readback_mu from the launch of the kernel that writes
+  // there until it has read the values: calls of other threads on the handle
+  // would otherwise leave their totals, which are used as sizes, in its place.
   void* readback = nullptr;
   void* readback_dev = nullptr;
+  std::mutex readback_mu;
   std::string err;
+  std::mutex err_mu;   // two threads' calls may fail at once
   // kernel timing (opt-in)
   struct Mark {
     int cls;
@@ -71,7 +77,10 @@ inline dsmp_status fail(dsmp_handle* h, dsmp_status st, const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(buf, sizeof(buf), fmt, ap);
   va_end(ap);
-  if (h) h->err = buf;
+  if (h) {
+    std::lock_guard<std::mutex> lock(h->err_mu);
+    h->err = buf;
+  }
   return st;
 }
 

@@ -913,6 +913,7 @@ extern "C" dsmp_status dsmp_subdomain_select(dsmp_handle* h, const float* pos, i
   ProfScope prof(h, DSMP_K_GATHER);
   hipStream_t s = h->stream;
   int32_t* counts = static_cast<int32_t*>(h->readback_dev);
+  std::lock_guard<std::mutex> lock(h->readback_mu);
   if (n <= SUB_SMALL) {
     hipLaunchKernelGGL(k_sub_small, dim3(1), dim3(1024), 0, s, pos, (int)n, (int)dim, b, idx_out, counts);
     DSMP_LAUNCHED(h, "sub-domain selection");

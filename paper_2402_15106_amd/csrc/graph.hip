@@ -1137,6 +1137,7 @@ dsmp_status count_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs
   }
   GraphStats* stats = static_cast<GraphStats*>(h->readback_dev);
   static_assert(sizeof(GraphStats) <= READBACK_BYTES, "fits the readback area");
+  std::unique_lock<std::mutex> lock(h->readback_mu);
   if (q->n_dst <= ROWS_PER * 1024) {
     hipLaunchKernelGGL(k_rows_single, dim3(1), dim3(1024), 0, s, w.rcnt, w.rraw, (int)q->n_dst, row_ptr, stats);
   } else {
@@ -1147,6 +1148,7 @@ dsmp_status count_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs
   DSMP_LAUNCHED(h, "row scan");
   DSMP_HIP(h, hipStreamSynchronize(s));
   const GraphStats hs = *static_cast<const GraphStats*>(h->readback);
+  lock.unlock();
   *E = (int64_t)hs.total;
   *maxraw = hs.maxraw;
   DSMP_CHECK(h, hs.maxraw <= (uint32_t)ROW_LIMIT, DSMP_UNSUPPORTED,

@@ -1,5 +1,8 @@
 """GPU parity: node sampling and radius graph against the oracle, bit for bit."""
 
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 
@@ -262,3 +265,59 @@ def test_graph_is_deterministic(env):
     b = lib.dsmp_radius_graph_build(pos, 20000, 0.05, 10)
     for x, y in ((a.row_ptr, b.row_ptr), (a.col, b.col), (a.csc_eid, b.csc_eid)):
         assert torch.equal(x, y)
+
+
+def test_two_threads_on_one_handle_get_their_own_totals(env):
+    """Graph builds and sub-domain selections of two host threads through one
+    handle, each with its own buffers and workspace (the library's C interface:
+    the binding keeps one workspace per handle)."""
+    dm, lib, torch = env
+    announce("two threads, one handle")
+    L, c = lib.lib, ctypes
+    lib._bind()
+
+    def graph_job(seed, n, r):
+        pos = torch.from_numpy(_rand(n, 2, seed)).cuda()
+        q, _ = lib._query(pos, n, r, 0, dm.CAP_KNN, 0)
+        nb = c.c_size_t()
+        assert L.dsmp_radius_graph_workspace(c.byref(q), c.byref(nb)) == dm.OK
+        ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
+        rp, _ = org.radius_graph(pos.cpu().numpy(), n, r)
+        E = c.c_int64()
+
+        def call():
+            st = L.dsmp_radius_graph_count(lib.h, c.byref(q), c.c_void_p(ws.data_ptr()), ws.numel(), c.byref(E))
+            return (st, E.value) == (dm.OK, int(rp[-1]))
+        return call, pos
+
+    def box_job(seed, n, hi):
+        pos_np = _rand(n, 2, seed)
+        pos = torch.from_numpy(pos_np).cuda()
+        nb, a, b = c.c_size_t(), c.c_int64(), c.c_int64()
+        assert L.dsmp_subdomain_workspace(n, c.byref(nb)) == dm.OK
+        ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
+        idx = torch.empty(n, dtype=torch.int32, device="cuda")
+        lo_c, hi_c = (c.c_float * 2)(0.0, 0.0), (c.c_float * 2)(hi, hi)
+        own = int((pos_np < np.float32(hi)).all(1).sum())
+
+        def call():
+            st = L.dsmp_subdomain_select(lib.h, c.c_void_p(pos.data_ptr()), n, 2, lo_c, hi_c, 0.0,
+                                         c.c_void_p(idx.data_ptr()), c.c_void_p(ws.data_ptr()), ws.numel(),
+                                         c.byref(a), c.byref(b))
+            return (st, a.value, b.value) == (dm.OK, own, own)
+        return call, pos
+
+    jobs = [[graph_job(50, 1000, 0.05), box_job(51, 3000, 0.4)], [graph_job(52, 20000, 0.01), box_job(53, 12000, 0.7)]]
+    torch.cuda.synchronize()
+    wrong = [0, 0]
+
+    def work(t):
+        for _ in range(200):
+            wrong[t] += sum(not call() for call, _ in jobs[t])
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert wrong == [0, 0]
