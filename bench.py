@@ -66,7 +66,7 @@ def parse():
 
 CPU_ROWS = {1: 1024, 2: 4096, 3: 2048, 4: 2048, 5: 4096}
 SRC_CORE = ["core.hip", "common.hpp"]
-SRC_GRAPH = ["graph.hip", "common.hpp"]
+SRC_GRAPH = ["graph.hip", "grid.hpp", "common.hpp"]
 SRC_FWD = ["nnconv_fwd.hip", "nnconv.hpp", "common.hpp"]
 SRC_BWD = ["nnconv_bwd.hip", "nnconv.hpp", "common.hpp"]
 SRC_AGG = ["nnconv_agg.hip", "nnconv.hpp", "common.hpp"]

@@ -150,6 +150,8 @@ dsmp_status dsmp_scatter_rows(dsmp_handle* h, const void* src, int64_t n, int64_
  * The radius test is float32 without fused multiply-add, in this order:
  *     dx_a = p_j[a] - p_i[a];  d2 = ((dx_0*dx_0) + (dx_1*dx_1)) [+ (dx_2*dx_2)]
  *     keep iff d2 <= r*r      (r*r rounded to float32)
+ * so a point with an infinite or NaN coordinate has no edges (unless r*r itself
+ * overflows), and the others have theirs.
  * Cap modes: DSMP_CAP_KNN keeps the `cap` smallest (d2, j) pairs;
  * DSMP_CAP_RANDOM keeps the `cap` smallest (key, j) pairs where key is the
  * SplitMix64 output number i*n_src + j + 1 after seeding with `seed`, a

@@ -10,6 +10,7 @@
 // Built with -ffp-contract=off; the distance test also spells out its
 // roundings with __fsub_rn / __fmul_rn / __fadd_rn.
 #include "common.hpp"
+#include "grid.hpp"
 
 using namespace dsmp;
 
@@ -17,13 +18,6 @@ namespace {
 
 constexpr int ROW_LIMIT = 4096;   // most sources within r of one destination
 constexpr int BBOX_BLOCKS = 256;
-
-struct GridParams {
-  float lo[3];
-  int dims[3];
-  int ncell;
-  double inv_c;   // 1 / cell width
-};
 
 struct GraphStats {
   unsigned long long total;   // sum of kept counts (64-bit, for the overflow check)
@@ -59,7 +53,7 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ 
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     float3 p = load_pos(pos, i, D);
     float v[3] = {p.x, p.y, p.z};
-    for (int a = 0; a < 3; ++a) { mn[a] = fminf(mn[a], v[a]); mx[a] = fmaxf(mx[a], v[a]); }
+    for (int a = 0; a < 3; ++a) box_add(mn[a], mx[a], v[a]);
   }
   for (int a = 0; a < 3; ++a) { sh[a][threadIdx.x] = mn[a]; sh[3 + a][threadIdx.x] = mx[a]; }
   __syncthreads();
@@ -72,33 +66,6 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ 
     __syncthreads();
   }
   if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = sh[threadIdx.x][0];
-}
-
-// Grid of the box [lo, hi].  Cells are at least r*(1 + 2^-10) wide, so two
-// points that pass the float32 radius test always sit in the same or adjacent
-// cells (cell coordinates are formed in double, see cell_coord); the grid is
-// coarsened by doubling until it has at most `cap` cells.
-__device__ __forceinline__ GridParams choose_grid(float lo[3], float hi[3], int D, float r, int64_t cap) {
-  for (int a = D; a < 3; ++a) { lo[a] = 0.0f; hi[a] = 0.0f; }
-  for (int a = 0; a < 3; ++a)
-    if (!(hi[a] >= lo[a])) { lo[a] = 0.0f; hi[a] = 0.0f; }   // empty input
-  double c = (double)r * (1.0 + 1.0 / 1024.0);
-  if (!(c > 1e-30)) c = 1e-30;
-  double dims[3];
-  for (;;) {
-    double cells = 1.0;
-    for (int a = 0; a < 3; ++a) {
-      dims[a] = floor(((double)hi[a] - (double)lo[a]) / c) + 1.0;
-      cells *= dims[a];
-    }
-    if (cells <= (double)cap) break;
-    c *= 2.0;
-  }
-  GridParams g;
-  for (int a = 0; a < 3; ++a) { g.lo[a] = lo[a]; g.dims[a] = (int)dims[a]; }
-  g.inv_c = 1.0 / c;
-  g.ncell = g.dims[0] * g.dims[1] * g.dims[2];
-  return g;
 }
 
 // One wave reduces the partial boxes, one lane chooses the grid.
@@ -117,24 +84,6 @@ __global__ void k_grid_setup(const float* __restrict__ part, int nb, int D, floa
       hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], o, 64));
     }
   if (lane == 0) *g = choose_grid(lo, hi, D, r, cap);
-}
-
-// Cell of coordinate v, in double: v - lo is exact there and the product
-// with 1/c is within 2^-52 of the cell coordinate, so the cell margin of
-// 2^-10 covers the rounding however many cells an axis has (in float32 the
-// worst-case error grows with the coordinate and reaches the margin at a few
-// thousand cells on an axis, which a long, thin point set can have).
-__device__ __forceinline__ int cell_coord(float v, float lo, double inv_c, int dim) {
-  const double t = ((double)v - (double)lo) * inv_c;
-  int c = (int)floor(t);
-  return c < 0 ? 0 : (c >= dim ? dim - 1 : c);
-}
-
-__device__ __forceinline__ uint32_t cell_of(float3 p, const GridParams& g, int D) {
-  const int cx = cell_coord(p.x, g.lo[0], g.inv_c, g.dims[0]);
-  const int cy = cell_coord(p.y, g.lo[1], g.inv_c, g.dims[1]);
-  const int cz = D == 3 ? cell_coord(p.z, g.lo[2], g.inv_c, g.dims[2]) : 0;
-  return (uint32_t)(cx + g.dims[0] * (cy + g.dims[1] * cz));
 }
 
 // The count that a point finds in its cell is its place there, so that the
@@ -192,8 +141,9 @@ __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ p
     const int i = u * 1024 + tid;
     if (i < n) {
       p[u] = load_pos(pos, i, D);
-      v[0] = fminf(v[0], p[u].x); v[1] = fminf(v[1], p[u].y); v[2] = fminf(v[2], p[u].z);
-      v[3] = fmaxf(v[3], p[u].x); v[4] = fmaxf(v[4], p[u].y); v[5] = fmaxf(v[5], p[u].z);
+      box_add(v[0], v[3], p[u].x);
+      box_add(v[1], v[4], p[u].y);
+      box_add(v[2], v[5], p[u].z);
     }
   }
 #pragma unroll

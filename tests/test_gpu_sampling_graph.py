@@ -258,6 +258,26 @@ def test_graph_workload_rows(env, k):
     _check_graph(lib, torch, pos, w.n_dst, w.r, w.cap, w.cap_mode, rows=rows)
 
 
+@pytest.mark.parametrize("n,n_dst,r,cap,mode", [(600, 500, 0.1, 0, 0), (600, 600, 0.1, 0, 0), (600, 500, 0.1, 6, 0),
+                                                (600, 500, 0.1, 6, 1), (8300, 400, 0.05, 0, 0),
+                                                (8300, 400, 0.05, 6, 0), (600, 500, 1e30, 30, 0)])
+def test_graph_of_coordinates_that_are_not_finite(env, n, n_dst, r, cap, mode):
+    """Both forms of the grid with infinite and NaN coordinates among the points:
+    such points have no edges, the others theirs (a radius whose square
+    overflows reaches the infinite ones too)."""
+    dm, lib, torch = env
+    announce("graph, infinite coordinates", n, n_dst, r, cap, mode)
+    pos = _rand(n, 3, 60)
+    pos[[3, n_dst - 1, n - 1], [0, 1, 2]] = np.inf
+    pos[[7, n - 2]] = -np.inf
+    pos[9, 1] = np.nan
+    with np.errstate(invalid="ignore", over="ignore"):
+        rp, col = org.radius_graph(pos, n_dst, r, cap, mode, 5, method="brute")
+    g = lib.dsmp_radius_graph_build(torch.from_numpy(pos).cuda(), n_dst, r, cap, mode, 5, capacity=int(rp[-1]))
+    assert np.array_equal(g.row_ptr.cpu().numpy(), rp) and np.array_equal(g.col.cpu().numpy()[:rp[-1]], col)
+    assert np.array_equal(g.csc_eid.cpu().numpy()[:rp[-1]], org.transpose(rp, col, n)[1])
+
+
 def test_graph_is_deterministic(env):
     dm, lib, torch = env
     pos = torch.from_numpy(_rand(20000, 3, 30)).cuda()
