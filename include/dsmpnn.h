@@ -204,6 +204,21 @@ dsmp_status dsmp_radius_graph_count(dsmp_handle* h, const dsmp_graph_query* q, v
 dsmp_status dsmp_radius_graph_build(dsmp_handle* h, const dsmp_graph_query* q, void* ws,
                                     size_t ws_bytes, int64_t edge_capacity, dsmp_graph* g);
 
+/* dsmp_radius_graph_build in two calls, for a caller that sizes the edge
+ * arrays by E: neither a count ahead of the build, which does most of the
+ * build's work a second time, nor arrays with room to spare.
+ * dsmp_radius_graph_rows SYNCHRONISES the stream and writes g->row_ptr (device
+ * [n_dst+1]; the other arrays are not read), g->n_dst, g->n_src, g->n_edges and
+ * *max_row (host), the largest row before the cap.  Errors as
+ * dsmp_radius_graph_count.  dsmp_radius_graph_edges queues the rest on the same
+ * stream, with the same query, max_row, and positions, workspace, row_ptr and
+ * counts as the first call left them; if g->n_edges > edge_capacity it returns
+ * DSMP_CAPACITY as dsmp_radius_graph_build does. */
+dsmp_status dsmp_radius_graph_rows(dsmp_handle* h, const dsmp_graph_query* q, void* ws, size_t ws_bytes,
+                                   dsmp_graph* g, int32_t* max_row);
+dsmp_status dsmp_radius_graph_edges(dsmp_handle* h, const dsmp_graph_query* q, void* ws, size_t ws_bytes,
+                                    int32_t max_row, int64_t edge_capacity, dsmp_graph* g);
+
 /* --------------------------------------------------------------- NNConv layer
  * The edge-conditioned convolution of eq. (1) / eq. (ii) with the residual
  * hop update of Algorithm 1.  For edge e = (i <- j) with attributes x_e:

@@ -34,6 +34,7 @@ EXPORTED = ["dsmp_version", "dsmp_create", "dsmp_destroy", "dsmp_set_stream", "d
             "dsmp_scatter_rows",
             "dsmp_subdomain_workspace", "dsmp_subdomain_select",
             "dsmp_radius_graph_workspace", "dsmp_radius_graph_count", "dsmp_radius_graph_build",
+            "dsmp_radius_graph_rows", "dsmp_radius_graph_edges",
             "dsmp_nnconv_packed_bytes", "dsmp_nnconv_pack", "dsmp_nnconv_workspace",
             "dsmp_nnconv_forward", "dsmp_nnconv_backward", "dsmp_profile_enable", "dsmp_profile_reset",
             "dsmp_profile_read", "dsmp_set_edge_algorithm", "dsmp_mlp_workspace", "dsmp_mlp_forward",
@@ -111,6 +112,10 @@ _SIG = {
     "dsmp_radius_graph_count": (ctypes.c_int, [_P, ctypes.POINTER(GraphQuery), _P, ctypes.c_size_t,
                                                ctypes.POINTER(ctypes.c_int64)]),
     "dsmp_radius_graph_build": (ctypes.c_int, [_P, ctypes.POINTER(GraphQuery), _P, ctypes.c_size_t,
+                                               ctypes.c_int64, ctypes.POINTER(CGraph)]),
+    "dsmp_radius_graph_rows": (ctypes.c_int, [_P, ctypes.POINTER(GraphQuery), _P, ctypes.c_size_t,
+                                              ctypes.POINTER(CGraph), ctypes.POINTER(ctypes.c_int32)]),
+    "dsmp_radius_graph_edges": (ctypes.c_int, [_P, ctypes.POINTER(GraphQuery), _P, ctypes.c_size_t, ctypes.c_int32,
                                                ctypes.c_int64, ctypes.POINTER(CGraph)]),
     "dsmp_nnconv_packed_bytes": (ctypes.c_int, [ctypes.POINTER(LayerDesc), ctypes.POINTER(ctypes.c_size_t)]),
     "dsmp_nnconv_pack": (ctypes.c_int, [_P, ctypes.POINTER(LayerDesc), ctypes.POINTER(LayerParams), _P]),
@@ -327,24 +332,25 @@ class Dsmp:
 
     def dsmp_radius_graph_build(self, pos, n_dst, r, cap=0, cap_mode=CAP_KNN, seed=0,
                                 capacity: Optional[int] = None, out: Optional[Graph] = None) -> Graph:
-        if out is None and capacity is None:
-            # room for 64 edges per destination (the cap, if lower) saves a counting
-            # call, which does most of the build's work; a graph with more says
-            # how many and is built again
-            guess = n_dst * min(cap, 64) if cap > 0 else n_dst * 64
-            try:
-                g = self.dsmp_radius_graph_build(pos, n_dst, r, cap, cap_mode, seed, capacity=guess)
-            except DsmpError as e:
-                if e.status != CAPACITY:
-                    raise
-                E = self.dsmp_radius_graph_count(pos, n_dst, r, cap, cap_mode, seed)
-                return self.dsmp_radius_graph_build(pos, n_dst, r, cap, cap_mode, seed, capacity=E)
-            n = max(g.n_edges, 1)
-            g.col, g.dst, g.csc_eid = g.col[:n], g.dst[:n], g.csc_eid[:n]
-            return g
         q, pos = self._query(pos, n_dst, r, cap, cap_mode, seed)
+        i32 = dict(dtype=torch.int32, device=self.device)
+        if out is None and capacity is None:
+            # the edge arrays allocated between the build's two halves, by the edge count
+            ws = self._graph_ws(q)
+            e = torch.empty(0, **i32)
+            out = Graph(n_dst, pos.shape[0], 0, torch.empty(n_dst + 1, **i32), e, e,
+                        torch.empty(pos.shape[0] + 1, **i32), e)
+            cg, max_row = out.c(), ctypes.c_int32()
+            self._bind()
+            self._check(self.lib.dsmp_radius_graph_rows(self.h, ctypes.byref(q), _ptr(ws), ws.numel(),
+                                                        ctypes.byref(cg), ctypes.byref(max_row)), self.h)
+            E = out.n_edges = cg.n_edges
+            out.col, out.dst, out.csc_eid = (torch.empty(max(E, 1), **i32) for _ in range(3))
+            cg.col, cg.dst, cg.csc_eid = out.col.data_ptr(), out.dst.data_ptr(), out.csc_eid.data_ptr()
+            self._check(self.lib.dsmp_radius_graph_edges(self.h, ctypes.byref(q), _ptr(ws), ws.numel(), max_row, E,
+                                                         ctypes.byref(cg)), self.h)
+            return out
         if out is None:
-            i32 = dict(dtype=torch.int32, device=self.device)
             out = Graph(n_dst, pos.shape[0], 0, torch.empty(n_dst + 1, **i32),
                         torch.empty(max(capacity, 1), **i32), torch.empty(max(capacity, 1), **i32),
                         torch.empty(pos.shape[0] + 1, **i32), torch.empty(max(capacity, 1), **i32))

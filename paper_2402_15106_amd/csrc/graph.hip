@@ -1129,31 +1129,47 @@ extern "C" dsmp_status dsmp_radius_graph_count(dsmp_handle* h, const dsmp_graph_
   return count_phase(h, q, w, w.rowptr_tmp, n_edges, &maxraw, false);
 }
 
-extern "C" dsmp_status dsmp_radius_graph_build(dsmp_handle* h, const dsmp_graph_query* q, void* ws,
-                                               size_t ws_bytes, int64_t edge_capacity, dsmp_graph* g) {
-  if (!h) return DSMP_INVALID_ARG;
+namespace {
+// What both halves of a build check of their arguments; the workspace carved.
+dsmp_status check_build(dsmp_handle* h, const dsmp_graph_query* q, void* ws, size_t ws_bytes, const dsmp_graph* g,
+                        GraphWs* w) {
   dsmp_status st = validate_query(h, q);
   if (st != DSMP_OK) return st;
   DSMP_CHECK(h, g != nullptr && g->row_ptr != nullptr, DSMP_INVALID_ARG, "graph or row_ptr is NULL");
+  size_t need;
+  *w = carve_graph_ws(ws, q, &need);
+  DSMP_CHECK(h, ws != nullptr && ws_bytes >= need, DSMP_WORKSPACE_TOO_SMALL,
+             "graph workspace needs %zu bytes", need);
+  return DSMP_OK;
+}
+
+dsmp_status check_edge_arrays(dsmp_handle* h, int64_t edge_capacity, const dsmp_graph* g) {
   DSMP_CHECK(h, edge_capacity >= 0, DSMP_INVALID_ARG, "negative edge capacity");
   DSMP_CHECK(h, edge_capacity == 0 || (g->col && g->dst), DSMP_INVALID_ARG, "col or dst is NULL");
   DSMP_CHECK(h, g->csc_ptr != nullptr && (edge_capacity == 0 || g->csc_eid), DSMP_INVALID_ARG,
              "csc arrays are NULL");
-  size_t need;
-  GraphWs w = carve_graph_ws(ws, q, &need);
-  DSMP_CHECK(h, ws != nullptr && ws_bytes >= need, DSMP_WORKSPACE_TOO_SMALL,
-             "graph workspace needs %zu bytes", need);
-  ProfScope prof(h, DSMP_K_GRAPH);
-  int64_t E;
-  uint32_t maxraw;
-  const bool select = fused_select(q);
-  // a symmetric graph (no cap, every source a destination) is its own transpose
-  const bool symmetric = q->cap == 0 && q->n_src == q->n_dst;
-  st = count_phase(h, q, w, g->row_ptr, &E, &maxraw, select);
+  return DSMP_OK;
+}
+
+// First half of a build: row_ptr, and in the workspace what the second half
+// reads (the sorted cells, for capped graphs the selected rows and in-degrees).
+dsmp_status rows_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs& w, dsmp_graph* g, uint32_t* maxraw) {
+  int64_t E = 0;
+  const dsmp_status st = count_phase(h, q, w, g->row_ptr, &E, maxraw, fused_select(q));
   g->n_dst = q->n_dst;
   g->n_src = q->n_src;
   g->n_edges = E;
-  if (st != DSMP_OK) return st;
+  return st;
+}
+
+// Second half: the rows' sources and the transpose of g->n_edges edges.
+dsmp_status edges_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs& w, uint32_t maxraw,
+                        int64_t edge_capacity, dsmp_graph* g) {
+  dsmp_status st;
+  const int64_t E = g->n_edges;
+  const bool select = fused_select(q);
+  // a symmetric graph (no cap, every source a destination) is its own transpose
+  const bool symmetric = q->cap == 0 && q->n_src == q->n_dst;
   hipStream_t s = h->stream;
   const float r2 = q->r * q->r;
   // in-degrees start at zero (the count phase zeroed them for the select pass)
@@ -1206,4 +1222,47 @@ extern "C" dsmp_status dsmp_radius_graph_build(dsmp_handle* h, const dsmp_graph_
     DSMP_LAUNCHED(h, "csc build");
   }
   return DSMP_OK;
+}
+
+}  // namespace
+
+extern "C" dsmp_status dsmp_radius_graph_build(dsmp_handle* h, const dsmp_graph_query* q, void* ws,
+                                               size_t ws_bytes, int64_t edge_capacity, dsmp_graph* g) {
+  if (!h) return DSMP_INVALID_ARG;
+  GraphWs w;
+  dsmp_status st;
+  if ((st = check_build(h, q, ws, ws_bytes, g, &w)) != DSMP_OK) return st;
+  if ((st = check_edge_arrays(h, edge_capacity, g)) != DSMP_OK) return st;
+  ProfScope prof(h, DSMP_K_GRAPH);
+  uint32_t maxraw;
+  if ((st = rows_phase(h, q, w, g, &maxraw)) != DSMP_OK) return st;
+  return edges_phase(h, q, w, maxraw, edge_capacity, g);
+}
+
+extern "C" dsmp_status dsmp_radius_graph_rows(dsmp_handle* h, const dsmp_graph_query* q, void* ws, size_t ws_bytes,
+                                              dsmp_graph* g, int32_t* max_row) {
+  if (!h) return DSMP_INVALID_ARG;
+  DSMP_CHECK(h, max_row != nullptr, DSMP_INVALID_ARG, "max_row is NULL");
+  GraphWs w;
+  dsmp_status st;
+  if ((st = check_build(h, q, ws, ws_bytes, g, &w)) != DSMP_OK) return st;
+  ProfScope prof(h, DSMP_K_GRAPH);
+  uint32_t maxraw;
+  if ((st = rows_phase(h, q, w, g, &maxraw)) != DSMP_OK) return st;
+  *max_row = (int32_t)maxraw;
+  return DSMP_OK;
+}
+
+extern "C" dsmp_status dsmp_radius_graph_edges(dsmp_handle* h, const dsmp_graph_query* q, void* ws, size_t ws_bytes,
+                                               int32_t max_row, int64_t edge_capacity, dsmp_graph* g) {
+  if (!h) return DSMP_INVALID_ARG;
+  GraphWs w;
+  dsmp_status st;
+  if ((st = check_build(h, q, ws, ws_bytes, g, &w)) != DSMP_OK) return st;
+  if ((st = check_edge_arrays(h, edge_capacity, g)) != DSMP_OK) return st;
+  DSMP_CHECK(h, max_row >= 0 && max_row <= ROW_LIMIT && g->n_dst == q->n_dst && g->n_src == q->n_src &&
+                 g->n_edges >= 0 && g->n_edges <= INT32_MAX, DSMP_INVALID_ARG,
+             "max_row and the graph are not those of dsmp_radius_graph_rows on this query");
+  ProfScope prof(h, DSMP_K_GRAPH);
+  return edges_phase(h, q, w, (uint32_t)max_row, edge_capacity, g);
 }

@@ -213,6 +213,54 @@ def test_graph_built_without_a_capacity(env, r, cap):
     assert np.array_equal(g.csc_eid[:E].cpu().numpy(), org.transpose(rp, col, 1000)[1])
 
 
+@pytest.mark.parametrize("r,cap", [(0.05, 0), (0.2, 0), (0.2, 80), (0.6, 20), (0.05, 5), (1e-6, 0)])
+def test_graph_built_without_a_capacity_counts_once_and_holds_its_edges(env, r, cap):
+    """Few and many edges per destination, every row selected and some left to
+    the fill: the arrays are as large as the graph, built by one pass over the
+    candidates."""
+    dm, lib, torch = env
+    announce("graph without capacity, memory", r, cap)
+    pos = torch.from_numpy(_rand(1000, 2, 41)).cuda()
+    E = lib.dsmp_radius_graph_count(pos, 1000, r, cap)
+    want = lib.dsmp_radius_graph_build(pos, 1000, r, cap, capacity=E)
+    lib.dsmp_profile_enable(True)
+    lib.dsmp_profile_reset()
+    try:
+        want2 = lib.dsmp_radius_graph_build(pos, 1000, r, cap, capacity=E, out=want)
+        one = lib.dsmp_profile_read()["graph"][1]
+        lib.dsmp_profile_reset()
+        g = lib.dsmp_radius_graph_build(pos, 1000, r, cap)
+        assert lib.dsmp_profile_read()["graph"][1] == 2 * one   # its two halves, each once
+    finally:
+        lib.dsmp_profile_enable(False)
+    assert g.n_edges == want2.n_edges == E
+    for a, b in ((g.row_ptr, want.row_ptr), (g.csc_ptr, want.csc_ptr)):
+        assert torch.equal(a, b)
+    for a, b in ((g.col, want.col), (g.dst, want.dst), (g.csc_eid, want.csc_eid)):
+        assert torch.equal(a[:E], b[:E]) and a.untyped_storage().nbytes() == 4 * max(E, 1)
+
+
+def test_graph_halves_check_their_arguments(env):
+    """The second half of a build with too little room, and with counts that are
+    not the first half's."""
+    dm, lib, torch = env
+    c, pos = ctypes, torch.from_numpy(_rand(1000, 2, 42)).cuda()
+    want = lib.dsmp_radius_graph_build(pos, 1000, 0.05, 0)
+    E = want.n_edges
+    q, _ = lib._query(pos, 1000, 0.05, 0, dm.CAP_KNN, 0)
+    ws = lib._graph_ws(q)
+    args = (lib.h, c.byref(q), c.c_void_p(ws.data_ptr()), ws.numel())
+    cg, row = want.c(), c.c_int32()
+    assert lib.lib.dsmp_radius_graph_rows(*args, c.byref(cg), None) == dm.INVALID_ARG
+    assert lib.lib.dsmp_radius_graph_rows(*args, c.byref(cg), c.byref(row)) == dm.OK
+    assert cg.n_edges == E and row.value == int(torch.diff(want.row_ptr).max())
+    assert lib.lib.dsmp_radius_graph_edges(*args, row, E - 1, c.byref(cg)) == dm.CAPACITY
+    assert lib.lib.dsmp_radius_graph_edges(*args, 5000, E, c.byref(cg)) == dm.INVALID_ARG
+    assert lib.lib.dsmp_radius_graph_edges(*args, -1, E, c.byref(cg)) == dm.INVALID_ARG
+    cg.n_dst = 999
+    assert lib.lib.dsmp_radius_graph_edges(*args, row, E, c.byref(cg)) == dm.INVALID_ARG
+
+
 @pytest.mark.parametrize("cap", [0, 10])
 def test_graph_capacity_error_reports_E(env, cap):
     dm, lib, torch = env
