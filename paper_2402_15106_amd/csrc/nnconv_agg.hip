@@ -61,7 +61,7 @@ __device__ __forceinline__ void put4_transposed(const uint4 (&v)[4], int kg, int
 struct OuterArgs {
   int64_t n_seg;               // segments: destinations (S) or sources (T)
   const int32_t* seg_ptr;      // [n_seg + 1] positions of each segment's edges
-  const int32_t* pos_eid;      // NULL: edge id = position; else edge id = pos_eid[position]
+  const int32_t* pos_eid;      // NULL: edge id = position; else edge id = pos_eid[position] (k_outer_sum_tr: NULL)
   const int32_t* row_of;       // gathered row of edge e
   const unsigned char* zE;     // [E][h2] layer dtype, stored order
   const unsigned char* u;      // gathered rows [*][d] layer dtype
@@ -766,6 +766,8 @@ dsmp_status outer_shape(dsmp_handle* h, const OuterArgs& a) {
   if constexpr (sizeof(T) == 2) {
     using S = OuterTrShape<DL, H2>;
     if constexpr (DL <= 64) {
+      DSMP_CHECK(h, a.pos_eid == nullptr, DSMP_UNSUPPORTED,
+                 "bf16 outer-product sums of d <= 64 take the edges in their stored order only");
       // chunks of 32 slots where the mean segment has no more edges
       const bool few = a.n_edges <= 32 * a.n_seg;
       auto kern = few ? (a.stream ? k_outer_sum_tr<DL, H2, 32, true> : k_outer_sum_tr<DL, H2, 32, false>)

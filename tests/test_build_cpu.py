@@ -49,3 +49,18 @@ def test_every_wave_waits_for_its_writes_before_the_hand_off(core_asm, kernel):
     assert ops and waits and waits[-1] > ops[-1], (kernel, code[ops[-1]], code[barrier])
     # and it is not skipped: no branch target between the wait and the barrier
     assert not any(l.endswith(":") for l in code[waits[-1]:barrier])
+
+
+def test_outer_sums_refuse_an_edge_order_they_do_not_read(tmp_path):
+    """The bf16 sums of d <= 64 take the edges in their stored order; a launch
+    with another order is refused on the host (nothing runs on a GPU here)."""
+    import paper_2402_15106_amd as dm
+    exe, libdir = str(tmp_path / "outer_order"), os.path.dirname(dm.LIB_PATH)
+    subprocess.run([build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17",
+                    os.path.join(ROOT, "tests", "native", "outer_order.cpp"), "-o", exe, "-L" + libdir, "-ldsmpnn",
+                    "-Wl,-rpath," + libdir], check=True, capture_output=True, timeout=300)
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1")
+    out = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=60, env=env).stdout.splitlines()
+    assert len(out) == 2
+    for line in out:
+        assert line.startswith("%d " % dm.UNSUPPORTED) and "stored order" in line
