@@ -250,7 +250,9 @@ extern "C" const char* dsmp_last_error(const dsmp_handle* h) { return h ? h->err
 // (the mix is a bijection of the counter), so exactly s are kept.  Three forms
 // by M, each bounded by the latency of its launches rather than by traffic:
 //   M <= 8,192        one workgroup does everything in one launch
-//                     (1,024 of 4,096: eleven launches of 56 us -> 7.2 us)
+//                     (1,024 of 4,096: eleven launches of 56 us -> 7.2 us; against
+//                     the next form 7.4 and 18.6 us at 4,096, 9.8 and 18.7 at
+//                     8,192, what the threads' registers hold)
 //   M <= 8,388,608    four launches (262,144 of 764,077: 95 -> 34 us): an 11-bit histogram, then one pass that
 //                     counts the sure candidates and lists those in the
 //                     threshold's bin (M / 2,048 on average), whose last

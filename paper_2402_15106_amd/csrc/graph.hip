@@ -118,7 +118,9 @@ __global__ __launch_bounds__(256) void k_cell_scatter(const float* __restrict__ 
 // gaps between them longer than that): points in registers, the box by wave
 // reductions, cell counts, places and starts in LDS (at most GRID_CELLS cells;
 // a finer grid is coarsened, which changes the candidates and no result).
-// 1,024 points: 18 us of kernels -> 6.7.
+// 1,024 points: 18 us of kernels -> 6.7; whole builds of 1,024, 4,096 and 8,192
+// points with this launch and with the six 38.8 and 70.8, 44.8 and 70.9, 55.1 and
+// 73.7 us (8,192 is what the registers and LDS hold).
 constexpr int GRID_SMALL = 8192, GRID_CELLS = 8192;
 __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ pos, int n, int D, float r, int cap,
                                                      GridParams* __restrict__ gp, int32_t* __restrict__ cstart,
@@ -315,7 +317,11 @@ __global__ __launch_bounds__(256) void k_nbr_count(const float* __restrict__ pos
 
 // The scan of the row counts into row_ptr, with the edge total (64-bit) and
 // the largest pre-cap count left in host memory for the call that waits for
-// them: one launch and no copy up to 16,384 rows, two launches above.
+// them: one launch and no copy up to 4,096 rows, two launches above.  The line
+// lies where the one workgroup's four rows per thread cost as much as the second
+// launch: whole builds of 1,024, 2,048, 3,000 and 4,096 rows in one launch and in
+// two 39.2 and 41.5, 40.3 and 42.1, 42.2 and 43.6, 45.0 and 45.6 us; with eight rows
+// per thread 6,000 54.1 and 50.1, with sixteen 16,384 88.5 and 71.0.
 __device__ __forceinline__ uint32_t block_max_1024(uint32_t v, uint32_t* sh) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -343,7 +349,7 @@ __device__ __forceinline__ void store_stats(GraphStats* st, unsigned long long t
   __threadfence_system();
 }
 
-constexpr int ROWS_PER = 16;   // rows per thread of the one-launch form
+constexpr int ROWS_PER = 4;   // rows per thread of the one-launch form
 __global__ __launch_bounds__(1024) void k_rows_single(const uint32_t* __restrict__ rcnt,
                                                       const uint32_t* __restrict__ rraw, int n,
                                                       int32_t* __restrict__ row_ptr, GraphStats* st) {

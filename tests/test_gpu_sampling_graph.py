@@ -184,7 +184,9 @@ CASES = {
     "near_coincident_knn40": (lambda: (np.repeat(_rand(10, 3, 37), 200, axis=0)
                                        + 1e-7 * _rand(2000, 3, 38)).astype(np.float32), 2000, 0.01, 40, 0),
     "complete_66_knn64": (lambda: _rand(66, 2, 39), 66, 5.0, 64, 0),
-    # row counts scanned in one launch (up to 16,384 rows) and in two
+    # row counts scanned in one launch (up to 4,096 rows) and in two
+    "2d_4096_rows": (lambda: _rand(4200, 2, 43), 4096, 0.03, 0, 0),
+    "2d_4097_rows_knn": (lambda: _rand(4200, 2, 44), 4097, 0.05, 9, 0),
     "2d_16384_rows": (lambda: _rand(16384, 2, 33), 16384, 0.02, 0, 0),
     "2d_16385_rows_knn": (lambda: _rand(16500, 2, 34), 16385, 0.03, 9, 0),
 }
