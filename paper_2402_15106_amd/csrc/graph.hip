@@ -125,8 +125,7 @@ constexpr int GRID_SMALL = 8192, GRID_CELLS = 8192;
 __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ pos, int n, int D, float r, int cap,
                                                      GridParams* __restrict__ gp, int32_t* __restrict__ cstart,
                                                      float4* __restrict__ spos, int32_t* __restrict__ sidx,
-                                                     uint32_t* __restrict__ za, int nza, uint32_t* __restrict__ zb,
-                                                     int nzb) {
+                                                     uint32_t* __restrict__ za, int nza) {
   __shared__ uint32_t cnt[GRID_CELLS];
   __shared__ float red[6][16];
   __shared__ uint32_t sh[32];
@@ -134,7 +133,6 @@ __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ p
   constexpr int PER = GRID_SMALL / 1024, CPT = GRID_CELLS / 1024;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   for (int i = tid; i < nza; i += 1024) za[i] = 0;
-  for (int i = tid; i < nzb; i += 1024) zb[i] = 0;
   for (int c = tid; c < GRID_CELLS; c += 1024) cnt[c] = 0;
   float3 p[PER];
   float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -1063,7 +1061,7 @@ dsmp_status count_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs
   if (n <= GRID_SMALL) {
     hipLaunchKernelGGL(k_grid_small, dim3(1), dim3(1024), 0, s, q->pos, (int)n, D, q->r,
                        (int)std::min<int64_t>(w.ncap, GRID_CELLS), w.grid, w.cstart, w.spos, w.sidx, zdeg,
-                       (int)nzdeg, nullptr, 0);
+                       (int)nzdeg);
     DSMP_LAUNCHED(h, "grid and cell sort");
   } else {
     const unsigned nb = std::min<unsigned>(ceil_div(n, 256), BBOX_BLOCKS);

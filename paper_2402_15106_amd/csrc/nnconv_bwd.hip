@@ -2920,12 +2920,10 @@ dsmp_status run_edge_grads(dsmp_handle* h, const DzArgs& dz, const W3Args& w3, c
         }
       }
       if constexpr (S::NSPLIT > 1 && H1 == 256 && H2 == 256) {
-        {
-          auto k2 = k_bwd_dW2_tr<H1, H2, true>;
-          if ((st = set_lds(h, k2, TS::LDS)) != DSMP_OK) return st;
-          ProfScope prof(h, DSMP_K_DW2);
-          hipLaunchKernelGGL(k2, dim3(nchunk), dim3(512), TS::LDS, s, w2);
-        }
+        auto k2 = k_bwd_dW2_tr<H1, H2, true>;
+        if ((st = set_lds(h, k2, TS::LDS)) != DSMP_OK) return st;
+        ProfScope prof(h, DSMP_K_DW2);
+        hipLaunchKernelGGL(k2, dim3(nchunk), dim3(512), TS::LDS, s, w2);
       } else {
         auto k2 = k_bwd_dW2_tr<H1, H2>;
         if ((st = set_lds(h, k2, TS::LDS)) != DSMP_OK) return st;

@@ -1,5 +1,6 @@
 """Host-side checks of bench.py's work model (no GPU)."""
 import os
+import subprocess
 import sys
 
 import pytest
@@ -42,3 +43,28 @@ def test_dz_bytes_of_the_feature_gradient_form():
     fl, by = bench.agg_work(S, E, 1100)["dz"]
     assert by == 1000 * (256 * 128 + 128) * 2 + E * (4 + 256 + 512 + 32 + 512 + 256)
     assert fl == 2 * E * (128 * 256 * 2) + 2 * 1000 * 128 * 128
+
+
+def test_the_work_model_takes_the_librarys_backward_forms(tmp_path):
+    """bench.dz_with_m states the library's rule a second time: the same answer at
+    both sides of its bounds (U past the last-level cache, 22 edges per
+    destination), as the library gives it on the host."""
+    import paper_2402_15106_amd as dm
+    from paper_2402_15106_amd import build
+    exe, libdir = str(tmp_path / "forms"), os.path.dirname(dm.LIB_PATH)
+    subprocess.run([build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17",
+                    os.path.join(ROOT, "tests", "native", "backward_forms.cpp"), "-o", exe, "-L" + libdir, "-ldsmpnn",
+                    "-Wl,-rpath," + libdir], check=True, capture_output=True, timeout=300)
+    cases = [(dt, d, n, E) for dt in ("f32", "bf16") for d in (32, 64, 128)
+             for n in (1000, 16384, 16385, 100000) for E in (0, 10 * n, 22 * n, 22 * n + 1, 40 * n)
+             if (dt, d) != ("f32", 128)]
+    text = "".join("%d %d %d %d\n" % (dm.BF16 if dt == "bf16" else dm.F32, d, n, E) for dt, d, n, E in cases)
+    out = subprocess.run([exe], input=text, check=True, capture_output=True, text=True, timeout=60).stdout.splitlines()
+    assert len(out) == len(cases)
+    for (dt, d, n, E), line in zip(cases, out):
+        class W:
+            pass
+        W.dtype, W.d, W.H1, W.H2 = dt, d, 2 * d, 2 * d
+        m, fused = (c == "1" for c in line.split())
+        assert bench.dz_with_m(W, E, n, False) == m, (dt, d, n, E)
+        assert not (m and fused)
