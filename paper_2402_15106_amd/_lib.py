@@ -335,20 +335,22 @@ class Dsmp:
         q, pos = self._query(pos, n_dst, r, cap, cap_mode, seed)
         i32 = dict(dtype=torch.int32, device=self.device)
         if out is None and capacity is None:
-            # the edge arrays allocated between the build's two halves, by the edge count
+            # the edge arrays allocated between the build's two halves, by the edge
+            # count; the GPU idles from the first half's end to the second's start,
+            # so all else is prepared ahead
             ws = self._graph_ws(q)
-            e = torch.empty(0, **i32)
-            out = Graph(n_dst, pos.shape[0], 0, torch.empty(n_dst + 1, **i32), e, e,
-                        torch.empty(pos.shape[0] + 1, **i32), e)
-            cg, max_row = out.c(), ctypes.c_int32()
+            row_ptr, e = torch.empty(n_dst + 1, **i32), torch.empty(0, **i32)
+            out = Graph(n_dst, pos.shape[0], 0, row_ptr, e, e, torch.empty(pos.shape[0] + 1, **i32), e)
+            cg, max_row, edges, new = out.c(), ctypes.c_int32(), self.lib.dsmp_radius_graph_edges, row_ptr.new_empty
+            args, cgp = (self.h, ctypes.byref(q), _ptr(ws), ws.numel()), ctypes.byref(cg)
             self._bind()
-            self._check(self.lib.dsmp_radius_graph_rows(self.h, ctypes.byref(q), _ptr(ws), ws.numel(),
-                                                        ctypes.byref(cg), ctypes.byref(max_row)), self.h)
-            E = out.n_edges = cg.n_edges
-            out.col, out.dst, out.csc_eid = (torch.empty(max(E, 1), **i32) for _ in range(3))
-            cg.col, cg.dst, cg.csc_eid = out.col.data_ptr(), out.dst.data_ptr(), out.csc_eid.data_ptr()
-            self._check(self.lib.dsmp_radius_graph_edges(self.h, ctypes.byref(q), _ptr(ws), ws.numel(), max_row, E,
-                                                         ctypes.byref(cg)), self.h)
+            self._check(self.lib.dsmp_radius_graph_rows(*args, cgp, ctypes.byref(max_row)), self.h)
+            E = cg.n_edges
+            n = E or 1
+            out.col, out.dst, out.csc_eid = col, dst, eid = new(n), new(n), new(n)
+            cg.col, cg.dst, cg.csc_eid = col.data_ptr(), dst.data_ptr(), eid.data_ptr()
+            self._check(edges(*args, max_row, E, cgp), self.h)
+            out.n_edges = E
             return out
         if out is None:
             out = Graph(n_dst, pos.shape[0], 0, torch.empty(n_dst + 1, **i32),
