@@ -157,7 +157,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32
 
 // Device-wide exclusive scan of n uint32 counts into out[0..n] (out[n] = total),
 // in one launch (up to 16,384), two (per-block sums, then per-block scans that
-// add up the sums ahead of them) or, above 4 M, three (a scan of the sums between).  tmp needs scan_tmp_elems(n) uint32.
+// add up the sums ahead of them) or, above 4 M, three (a scan of the sums
+// between).  tmp needs scan_tmp_elems(n) uint32.
 constexpr int SCAN_BLOCK = 1024;
 inline size_t scan_tmp_elems(int64_t n) { return (size_t)ceil_div(n, SCAN_BLOCK) + 1; }
 dsmp_status exclusive_scan_u32(dsmp_handle* h, const uint32_t* in, int32_t* out, int64_t n,

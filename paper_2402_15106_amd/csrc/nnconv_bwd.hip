@@ -2381,14 +2381,14 @@ __global__ __launch_bounds__(256) void k_dh_gather(int64_t n_src, int64_t n_dst,
 // both: at d = 64, 100,000 destinations of 10.8 edges, 475 us for 1.64 GB of U
 // and 0.85 GB of rows (5.2 TB/s), where the fused pass and k_dh_u take 472 and
 // 427 us.  m_e and da2 leave in 64- and 128-byte pieces of their rows: 8- and
-// 32-byte ones took 529 us (5,750 against 5,650 at 262,144 destinations, d = 128).
-// U_i and g_i are copied to LDS as they stand (direct
+// 32-byte ones took 529 us (at 262,144 destinations, d = 128, 5,750 and 5,650,
+// no more than cards and runs differ).  U_i and g_i are copied to LDS as they stand (direct
 // global-to-LDS loads, double-buffered over destinations).  Of the d / 32
 // waves, wave w takes, for every 32-edge tile of the destination, the two
 // 32-neuron tiles 2w, 2w + 1 of dz (A = U_i fragments read from LDS as
 // stored, B = h_j rows), which it masks with the forward's ReLU bits of z
 // into da2 (stored positions, as the dz pass does), and the 32-column tile w
-// of m_e (as k_dh_u).  dz1 = W2^T da2 and da1 follow in k_da1, whose W2^T
+// of m_e (as k_dh_u).  dz1 = W2^T da2 and da1 follow in k_da1_dw1, whose W2^T
 // copy would not fit in LDS beside two U_i.
 struct DzDhuArgs {
   DhuArgs m;
