@@ -86,6 +86,9 @@ __global__ void k_grid_setup(const float* __restrict__ part, int nb, int D, floa
   if (lane == 0) *g = choose_grid(lo, hi, D, r, cap);
 }
 
+// Most cells of a grid over n points.
+constexpr int64_t grid_cells_cap(int64_t n) { return 2 * n + 64; }
+
 // The count that a point finds in its cell is its place there, so that the
 // scatter needs no atomics of its own (285,564 points: 28 + 43 us -> 30 + 6).
 __global__ __launch_bounds__(256) void k_cell_hash(const float* __restrict__ pos, int64_t n, int D,
@@ -116,12 +119,14 @@ __global__ __launch_bounds__(256) void k_cell_scatter(const float* __restrict__ 
 // The grid and the cell sort of up to GRID_SMALL points by one workgroup, in
 // one launch in place of six (each of them 2 to 4 us at such sizes, with the
 // gaps between them longer than that): points in registers, the box by wave
-// reductions, cell counts, places and starts in LDS (at most GRID_CELLS cells;
-// a finer grid is coarsened, which changes the candidates and no result).
+// reductions, cell counts, places and starts in LDS, whose table holds as many
+// cells as the other form's (with 8,192 of them a grid of more was coarsened and
+// its destinations tested up to eight times the candidates: 8,192 points in 15,625
+// cells, 90 % of them in 512, 121 against 86 us for the build).
 // 1,024 points: 18 us of kernels -> 6.7; whole builds of 1,024, 4,096 and 8,192
-// points with this launch and with the six 38.8 and 70.8, 44.8 and 70.9, 55.1 and
+// points with this launch and with the six 38.8 and 70.8, 44.8 and 70.9, 56.0 and
 // 73.7 us (8,192 is what the registers and LDS hold).
-constexpr int GRID_SMALL = 8192, GRID_CELLS = 8192;
+constexpr int GRID_SMALL = 8192, GRID_CELLS = (int)grid_cells_cap(GRID_SMALL);
 __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ pos, int n, int D, float r, int cap,
                                                      GridParams* __restrict__ gp, int32_t* __restrict__ cstart,
                                                      float4* __restrict__ spos, int32_t* __restrict__ sidx,
@@ -130,10 +135,10 @@ __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ p
   __shared__ float red[6][16];
   __shared__ uint32_t sh[32];
   __shared__ GridParams gs;
-  constexpr int PER = GRID_SMALL / 1024, CPT = GRID_CELLS / 1024;
+  constexpr int PER = GRID_SMALL / 1024, CPT = GRID_CELLS / 1024 + 1;   // one thread's cells reach past the last
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   for (int i = tid; i < nza; i += 1024) za[i] = 0;
-  for (int c = tid; c < GRID_CELLS; c += 1024) cnt[c] = 0;
+  for (int c = tid; c < cap; c += 1024) cnt[c] = 0;
   float3 p[PER];
   float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
@@ -182,17 +187,16 @@ __global__ __launch_bounds__(1024) void k_grid_small(const float* __restrict__ p
   uint32_t c[CPT], sum = 0, tot;
 #pragma unroll
   for (int k = 0; k < CPT; ++k) {
-    c[k] = cnt[tid * CPT + k];
+    c[k] = tid * CPT + k < g.ncell ? cnt[tid * CPT + k] : 0u;
     sum += c[k];
   }
   uint32_t run = block_exclusive_scan_1024(sum, sh, &tot);   // every count is read when it returns
 #pragma unroll
   for (int k = 0; k < CPT; ++k) {
-    cnt[tid * CPT + k] = run;
+    if (tid * CPT + k < g.ncell) cnt[tid * CPT + k] = run;
     if (tid * CPT + k <= g.ncell) cstart[tid * CPT + k] = (int32_t)run;
     run += c[k];
   }
-  if (tid == 0) cstart[g.ncell] = n;   // not among the above when every cell of the table is used
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < PER; ++u)
@@ -1008,7 +1012,7 @@ GraphWs carve_graph_ws(void* base, const dsmp_graph_query* q, size_t* used) {
   const int64_t n_src = q->n_src, n_dst = q->n_dst;
   Carve c(base);
   GraphWs w;
-  w.ncap = 2 * n_src + 64;
+  w.ncap = grid_cells_cap(n_src);
   w.part = c.take<float>(BBOX_BLOCKS * 6);
   w.grid = c.take<GridParams>(1);
   w.cellid = c.take<uint32_t>(n_src);
@@ -1060,7 +1064,7 @@ dsmp_status count_phase(dsmp_handle* h, const dsmp_graph_query* q, const GraphWs
   const int64_t nzdeg = select ? (w.scur - w.indeg) + n : 0;
   if (n <= GRID_SMALL) {
     hipLaunchKernelGGL(k_grid_small, dim3(1), dim3(1024), 0, s, q->pos, (int)n, D, q->r,
-                       (int)std::min<int64_t>(w.ncap, GRID_CELLS), w.grid, w.cstart, w.spos, w.sidx, zdeg,
+                       (int)w.ncap, w.grid, w.cstart, w.spos, w.sidx, zdeg,
                        (int)nzdeg);
     DSMP_LAUNCHED(h, "grid and cell sort");
   } else {

@@ -173,6 +173,10 @@ CASES = {
     # grid of more cells than its table; and one point more
     "sparse_8192_points": (lambda: _rand(8192, 2, 30), 8192, 0.004, 0, 0),
     "sparse_8193_points": (lambda: _rand(8193, 2, 31), 8193, 0.004, 0, 0),
+    # more cells than points at one radius (12,996), in 2-D and, crowded in a corner, 3-D
+    "8192_points_13k_cells": (lambda: _rand(8192, 2, 45), 8192, 0.00877, 0, 0),
+    "8000_points_16k_cells_crowded": (lambda: np.concatenate([_rand(800, 3, 46), 0.2 * _rand(7200, 3, 47)]),
+                                      8000, 0.0405, 24, 0),
     "8193_points_halo_random": (lambda: _rand(8193, 3, 32), 7000, 0.07, 6, 1),
     # the cap among shells of equal and nearly equal distances (a lattice), among
     # more equal distances than are ranked one per lane (coincident points, and
