@@ -177,4 +177,15 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t c) {
   return z ^ (z >> 31);
 }
 
+// The counter c of splitmix64(seed, c) == z, step by step backwards (the
+// multipliers are the inverses of those above modulo 2^64).
+__device__ __forceinline__ uint64_t splitmix64_counter(uint64_t seed, uint64_t z) {
+  z ^= (z >> 31) ^ (z >> 62);
+  z *= 0x319642B2D24D8EC3ull;
+  z ^= (z >> 27) ^ (z >> 54);
+  z *= 0x96DE1B173F119089ull;
+  z ^= (z >> 30) ^ (z >> 60);
+  return (z - seed) * 0xF1DE83E19937733Dull - 1ull;
+}
+
 }  // namespace dsmp

@@ -498,9 +498,9 @@ constexpr int SEL_PER_LANE = 8;
 
 // The one-pass select of capped graphs: caps up to FUSE_CAP, rows of up to
 // FUSE_LIM candidates (larger rows are built by the fill kernel).
-// Without the payload array of the random cap (a nearest-neighbour key holds
-// its source index) 512 candidates take 16 KB per block of four rows, which
-// still lets eight blocks on a CU.  With 256 an eighth of the rows of a mesh
+// Without an array of payloads (a nearest-neighbour key holds its source index,
+// a random one is the hash of a counter that has it) 512 candidates take 16 KB
+// per block of four rows, which still lets eight blocks on a CU.  With 256 an eighth of the rows of a mesh
 // crowded toward a wall (32,768 nodes, mean 78 candidates) was left to the
 // fill kernel and the transpose to a scatter: 113 -> 59 us for select, fill,
 // placing and scatter.
@@ -515,12 +515,10 @@ constexpr int FUSE_LIM = 512;
 // the fixed bits; the kept keys are those whose fixed bits are at most K's.
 // The high words decide unless two of them are equal at K; only then are the
 // low words visited.
-// val NULL: a key's low word is its payload.
-template <int NT>
-__device__ __forceinline__ void select_cap_bits(const uint64_t* key, const int32_t* val, uint32_t* js,
-                                           int n, int cap, int lane) {
+// pay(u, high word, low word) is the payload of key u.
+template <int NT, typename Pay>
+__device__ __forceinline__ void select_cap_bits(const uint64_t* key, Pay pay, uint32_t* js, int n, int cap, int lane) {
   uint32_t kh[NT], kl[NT];
-  int32_t vr[NT];
   uint64_t vm[NT];  // lanes that hold a key (wave-uniform)
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -529,7 +527,6 @@ __device__ __forceinline__ void select_cap_bits(const uint64_t* key, const int32
     const uint64_t k = ok ? key[u] : ~0ull;
     kh[t] = (uint32_t)(k >> 32);
     kl[t] = (uint32_t)k;
-    vr[t] = val ? (ok ? val[u] : 0) : (int32_t)kl[t];
     vm[t] = __ballot(ok);
   }
   int rank = cap - 1;  // K's rank among the keys that match the fixed bits
@@ -572,7 +569,7 @@ __device__ __forceinline__ void select_cap_bits(const uint64_t* key, const int32
     const bool keep = h < ph || (h == ph && (kl[t] & ml) <= pl);
     const uint64_t bm = __ballot(keep) & vm[t];
     const int slot = m0 + __popcll(bm & ((1ull << lane) - 1ull));
-    if (((bm >> lane) & 1ull) && slot < cap) js[slot] = (uint32_t)vr[t];
+    if (((bm >> lane) & 1ull) && slot < cap) js[slot] = pay(lane + 64 * t, kh[t], kl[t]);
     m0 += __popcll(bm);
   }
 }
@@ -587,8 +584,8 @@ __device__ __forceinline__ void select_cap_bits(const uint64_t* key, const int32
 // separates (after SEL_PROBES) are left to the bits.  frac: the share of the
 // range [0, top] expected to hold the cap smallest of the n keys.
 constexpr int SEL_RANK = 32, SEL_PROBES = 8;
-template <int NT, bool FLOATS>
-__device__ __forceinline__ void select_cap(uint64_t* key, const int32_t* val, uint32_t* js, int n, int cap, int lane,
+template <int NT, bool FLOATS, typename Pay>
+__device__ __forceinline__ void select_cap(uint64_t* key, Pay pay, uint32_t* js, int n, int cap, int lane,
                                            uint32_t top, float frac) {
   uint32_t kh[NT];
 #pragma unroll
@@ -627,47 +624,36 @@ __device__ __forceinline__ void select_cap(uint64_t* key, const int32_t* val, ui
   }
   const int m = ch - cl, need = cap - cl;   // keys of the bracket, and how many of them are kept
   if (m > 64 && need != m) {
-    select_cap_bits<NT>(key, val, js, n, cap, lane);
+    select_cap_bits<NT>(key, pay, js, n, cap, lane);
     return;
   }
-  // the payloads, then the keys below the bracket to js and the bracket's keys
-  // and payloads to the front of the key array, one per lane
+  // the payloads of the keys below the bracket to js and the bracket's keys to
+  // the front of the key array, one per lane
   uint32_t kl[NT];
-  int32_t vr[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int u = lane + 64 * t;
     kl[t] = u < n ? (uint32_t)key[u] : 0u;
-    vr[t] = val ? (u < n ? val[u] : 0) : (int32_t)kl[t];
   }
   wave_sync();   // every key is read; js and the bracket overwrite them
   // js takes the first cap (at most 64) words, 256 bytes; the bracket's keys lie
-  // behind them (64 keys of 8 bytes at 256), their payloads behind those
+  // behind them (64 keys of 8 bytes at 256)
   uint64_t* bk = key + 32;
-  uint32_t* bv = reinterpret_cast<uint32_t*>(key + 96);
   int s0 = 0, b0 = 0;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const bool in = lane + 64 * t < n, low = in && below && kh[t] <= lo, mid = in && !low && kh[t] <= hi;
     const uint64_t ml = __ballot(low), mm = __ballot(mid);
     const uint64_t before = (1ull << lane) - 1ull;
-    if (low) js[s0 + __popcll(ml & before)] = (uint32_t)vr[t];
-    if (mid) {
-      const int at = b0 + __popcll(mm & before);
-      if (need == m) {
-        js[cl + at] = (uint32_t)vr[t];
-      } else {
-        bk[at] = ((uint64_t)kh[t] << 32) | kl[t];
-        bv[at] = (uint32_t)vr[t];
-      }
-    }
+    const int at = (low ? s0 : need == m ? cl + b0 : b0) + __popcll((low ? ml : mm) & before);
+    if (low || (mid && need == m)) js[at] = pay(lane + 64 * t, kh[t], kl[t]);
+    else if (mid) bk[at] = ((uint64_t)kh[t] << 32) | kl[t];
     s0 += __popcll(ml);
     b0 += __popcll(mm);
   }
   if (need == m) return;
   wave_sync();
   const uint64_t mine = lane < m ? bk[lane] : ~0ull;
-  const uint32_t pay = lane < m ? bv[lane] : 0u;
   const uint32_t mh = (uint32_t)(mine >> 32), mw = (uint32_t)mine;
   int rank = 0;
   for (int k = 0; k < m; ++k) {
@@ -675,7 +661,7 @@ __device__ __forceinline__ void select_cap(uint64_t* key, const int32_t* val, ui
     const uint32_t ow = (uint32_t)__builtin_amdgcn_readlane((int)mw, k);
     rank += oh < mh || (oh == mh && ow < mw);
   }
-  if (lane < m && rank < need) js[cl + rank] = pay;
+  if (lane < m && rank < need) js[cl + rank] = pay(lane, mh, mw);
 }
 
 // One wave per destination row, up to four rows per block (each wave with
@@ -729,15 +715,16 @@ __global__ __launch_bounds__(256) void k_nbr_fill(const float* __restrict__ pos,
   wave_sync();
   uint32_t* js = reinterpret_cast<uint32_t*>(key);   // kept sources (the key array reused as uint32 scratch)
   if (cap > 0 && n > cap && n <= 64 * SEL_PER_LANE) {
+    auto pay = [&](int u, uint32_t, uint32_t) { return (uint32_t)val[u]; };
     switch ((n + 63) >> 6) {
-      case 1: select_cap_bits<1>(key, val, js, n, cap, lane); break;
-      case 2: select_cap_bits<2>(key, val, js, n, cap, lane); break;
-      case 3: select_cap_bits<3>(key, val, js, n, cap, lane); break;
-      case 4: select_cap_bits<4>(key, val, js, n, cap, lane); break;
-      case 5: select_cap_bits<5>(key, val, js, n, cap, lane); break;
-      case 6: select_cap_bits<6>(key, val, js, n, cap, lane); break;
-      case 7: select_cap_bits<7>(key, val, js, n, cap, lane); break;
-      default: select_cap_bits<8>(key, val, js, n, cap, lane); break;
+      case 1: select_cap_bits<1>(key, pay, js, n, cap, lane); break;
+      case 2: select_cap_bits<2>(key, pay, js, n, cap, lane); break;
+      case 3: select_cap_bits<3>(key, pay, js, n, cap, lane); break;
+      case 4: select_cap_bits<4>(key, pay, js, n, cap, lane); break;
+      case 5: select_cap_bits<5>(key, pay, js, n, cap, lane); break;
+      case 6: select_cap_bits<6>(key, pay, js, n, cap, lane); break;
+      case 7: select_cap_bits<7>(key, pay, js, n, cap, lane); break;
+      default: select_cap_bits<8>(key, pay, js, n, cap, lane); break;
     }
     n = cap;
   } else {
@@ -888,13 +875,11 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
                                                     uint32_t* __restrict__ indeg,
                                                     uint32_t* __restrict__ eslot) {
   __shared__ uint64_t skey[4][FUSE_LIM];
-  __shared__ int32_t sval[KNN ? 1 : 4][KNN ? 1 : FUSE_LIM];
   const int wv = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int64_t i = (int64_t)blockIdx.x * 4 + wv;
   if (i >= n_dst) return;
   uint64_t* key = skey[wv];
-  int32_t* val = KNN ? nullptr : sval[KNN ? 0 : wv];
   const GridParams g = *gp;
   const float3 pi = load_pos(pos, i, D);
   const Candidates c = candidate_ranges(pi, D, g, cstart, lane);
@@ -908,7 +893,6 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
       if (slot < FUSE_LIM) {
         key[slot] = KNN ? (((uint64_t)__float_as_uint(d2)) << 32) | (uint32_t)j
                         : splitmix64(seed, (uint64_t)i * (uint64_t)n_src + (uint64_t)j);
-        if constexpr (!KNN) val[slot] = j;
       }
     }
     n += __popcll(m);
@@ -921,6 +905,11 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
   if (n > FUSE_LIM) return;
   wave_sync();
   uint32_t* js = reinterpret_cast<uint32_t*>(key);  // kept sources, over the keys
+  // a key's source: its low word, or from the counter i * n_src + j that it is the hash of
+  auto pay = [&](int, uint32_t kh, uint32_t kl) {
+    if constexpr (KNN) return kl;
+    else return (uint32_t)splitmix64_counter(seed, ((uint64_t)kh << 32) | kl) - (uint32_t)((uint64_t)i * (uint64_t)n_src);
+  };
   if (n > cap) {
     // squared distances: the cap nearest of n in a ball of D dimensions lie within
     // (cap / n)^(2/D) of its squared radius; hashed keys are uniform
@@ -928,19 +917,17 @@ __global__ __launch_bounds__(256) void k_nbr_select(const float* __restrict__ po
     const float frac = KNN && D == 3 ? __builtin_amdgcn_exp2f(0.6666667f * __builtin_amdgcn_logf(share)) : share;
     const uint32_t top = KNN ? __float_as_uint(r2) : 0xFFFFFFFFu;
     switch ((n + 63) >> 6) {
-      case 1: select_cap<1, KNN>(key, val, js, n, cap, lane, top, frac); break;
-      case 2: select_cap<2, KNN>(key, val, js, n, cap, lane, top, frac); break;
-      case 3: select_cap<3, KNN>(key, val, js, n, cap, lane, top, frac); break;
-      case 4: select_cap<4, KNN>(key, val, js, n, cap, lane, top, frac); break;
-      case 5: case 6: select_cap<6, KNN>(key, val, js, n, cap, lane, top, frac); break;
-      default: select_cap<8, KNN>(key, val, js, n, cap, lane, top, frac); break;
+      case 1: select_cap<1, KNN>(key, pay, js, n, cap, lane, top, frac); break;
+      case 2: select_cap<2, KNN>(key, pay, js, n, cap, lane, top, frac); break;
+      case 3: select_cap<3, KNN>(key, pay, js, n, cap, lane, top, frac); break;
+      case 4: select_cap<4, KNN>(key, pay, js, n, cap, lane, top, frac); break;
+      case 5: case 6: select_cap<6, KNN>(key, pay, js, n, cap, lane, top, frac); break;
+      default: select_cap<8, KNN>(key, pay, js, n, cap, lane, top, frac); break;
     }
-  } else if constexpr (KNN) {
-    const uint32_t j = lane < n ? (uint32_t)key[lane] : 0u;   // n <= cap <= 64
-    wave_sync();   // js overwrites the keys
-    if (lane < n) js[lane] = j;
   } else {
-    for (int t = lane; t < n; t += 64) js[t] = (uint32_t)val[t];
+    const uint64_t k = lane < n ? key[lane] : 0ull;   // n <= cap <= 64
+    wave_sync();   // js overwrites the keys
+    if (lane < n) js[lane] = pay(lane, (uint32_t)(k >> 32), (uint32_t)k);
   }
   wave_sync();
   // kept <= cap <= 64: sorted in registers
