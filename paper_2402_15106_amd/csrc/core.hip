@@ -723,12 +723,15 @@ extern "C" dsmp_status dsmp_sample_nodes_noalloc(dsmp_handle* h, int64_t M, int6
 // ------------------------------------------------------------------ gather
 
 namespace {
-// One thread per unit: a 16-byte unit where the rows and both arrays are
+// A thread per unit: a 16-byte unit where the rows and both arrays are
 // aligned to it, else a word.  Indices are 32-bit below 2^31 units (the row of
 // a unit is then one short division, a shift where a row is a power of two of
 // units).  Gathers of 262,144 rows of 12, 16 and 256 bytes: 42.6 -> 30.5 us
 // together, the last at 5.8 TB/s read and written (words with 64-bit divisions
-// before).
+// before).  At most GATHER_GRID workgroups, eight per CU, which step over the
+// rest: with a workgroup for every 256 units 150,000 rows of 132 bytes take 14.2
+// us, with 8,192 12.3 and with 2,048 11.4; rows of 16-byte units are the same.
+constexpr int64_t GATHER_GRID = 2048;
 template <typename U, typename I>
 __global__ __launch_bounds__(256) void k_gather_rows(const U* __restrict__ src, int64_t n_src_rows, I units, int sh,
                                                      const int32_t* __restrict__ idx, I total, U* __restrict__ dst) {
@@ -744,7 +747,7 @@ void gather_launch(hipStream_t st, const void* src, int64_t n_src_rows, int64_t 
                    int64_t n, void* dst) {
   const int64_t units = row_bytes / (int64_t)sizeof(U), total = n * units;
   const int sh = (units & (units - 1)) == 0 ? __builtin_ctzll((unsigned long long)units) : -1;
-  const unsigned g = (unsigned)std::min<int64_t>((total + 255) / 256, 1 << 22);
+  const unsigned g = (unsigned)std::min<int64_t>((total + 255) / 256, GATHER_GRID);
   if (total < (1ll << 31))   // a step past the end stays below 2^32
     hipLaunchKernelGGL((k_gather_rows<U, uint32_t>), dim3(g), dim3(256), 0, st, static_cast<const U*>(src),
                        n_src_rows, (uint32_t)units, sh, idx, (uint32_t)total, static_cast<U*>(dst));

@@ -55,6 +55,16 @@ def test_gather_rows_units(env, cols, offset):
     assert torch.equal(out, want)
 
 
+@pytest.mark.parametrize("cols", [33, 64])
+def test_gather_rows_in_several_steps(env, cols):
+    """More units than the launch has threads, the last step part-filled."""
+    dm, lib, torch = env
+    announce("gather in steps", cols)
+    src = torch.rand(1000, cols, device="cuda")
+    idx = torch.randint(0, 1000, (70001,), device="cuda", dtype=torch.int32)
+    assert torch.equal(lib.dsmp_gather_rows(src, idx), src[idx.long()])
+
+
 def test_sampling_rejects_bad_sizes(env):
     dm, lib, torch = env
     with pytest.raises(dm.DsmpError) as ei:
