@@ -680,11 +680,11 @@ __global__ __launch_bounds__(256, (DL <= 64 && H2 * sizeof(T) <= 256) ? 3 : 1) v
 // One pass over 32-edge tiles computes dz = U_i h_j, the masked da2,
 // dz1 = W2^T da2 and da1 (as k_bwd_dz_agg does), and folds the per-edge
 // weight gradients straight into per-workgroup sums, so da2 and da1 never go
-// to HBM.  A workgroup takes blocks of nb destinations; a tile is 32
-// consecutive edges of the block's rows, so it may cross destinations: dz
-// runs once per destination in the tile, with the B operand restricted to
-// that destination's lanes (every tile is full but the block's last, where a
-// tile per destination would leave most tails part-empty).  The sums:
+// to HBM.  A workgroup takes a range of the edges, as even as they come; a
+// tile is 32 consecutive edges, so it may cross destinations: dz runs once per
+// destination in the tile, with the B operand restricted to that destination's
+// lanes (every tile is full but the last, where a tile per destination would
+// leave most tails part-empty).  The sums:
 //   dW2[k][j] = sum_e da2_e[k] z1_e[j],  db2 = sum_e da2_e,
 //   dW1[j][c] = sum_e da1_e[j] x_e[c],   db1 = sum_e da1_e.
 // A workgroup of eight waves takes four tiles per round; the two waves of a
@@ -704,7 +704,6 @@ __global__ __launch_bounds__(256, (DL <= 64 && H2 * sizeof(T) <= 256) ? 3 : 1) v
 // while the products run; the barriers order LDS traffic only.
 // Partial sums go to slot blockIdx.x of the dW2/db2 and dW1/db1 partial
 // buffers, summed later in a fixed order.
-constexpr int EG_NB = 60;   // row pointers of a block fit one wave
 struct EdgeGradArgs {
   DzArgs dz;
   const float* node_attr;
@@ -712,7 +711,7 @@ struct EdgeGradArgs {
   unsigned char* da1_out;   // [E][h1] bf16 permuted order, or null (needed for the attribute gradient)
   float* p_w2;              // [gridDim.x][h2*h1 + h2]
   float* p_w1;              // [gridDim.x][h1*de + h1]
-  int nb;                   // destinations per block, 1 .. EG_NB
+  int unit;                 // the edges are dealt out in units of this many (whole tiles)
 };
 
 template <int DL, int H1, int H2>
@@ -771,10 +770,41 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
   for (int m = 0; m < G::TPW; ++m)
     if (active && kt_of(m) % JT == jt) bm = m;
   float db2 = 0.0f;   // the lane's half of the edges, column kt(bm)*32 + l32
+  // a tile: 32 consecutive edges of the workgroup's range (rows in order), which
+  // may span several destinations: the lane's edge, its source and its destination
+  struct Tile {
+    int eid, cnt, jn, dn;   // graph indices are int32
+    bool has, valid;
+  };
+  const int64_t nu = (a.E + g.unit - 1) / g.unit;
+  const int e_beg = (int)(nu * blockIdx.x / gridDim.x * g.unit);
+  const int64_t e_to = nu * (blockIdx.x + 1) / gridDim.x * g.unit;
+  const int e_end = (int)(e_to < a.E ? e_to : a.E);
+  const int ntile = (e_end - e_beg + 31) / 32;
+  auto locate = [&](int tau, Tile& t) {
+    t.has = tau < ntile;
+    t.eid = 0; t.cnt = 0; t.valid = false;
+    if (!t.has) return;
+    const int c0 = e_beg + tau * 32;
+    t.eid = c0 + l32;
+    t.valid = t.eid < e_end;
+    t.cnt = e_end - c0 < 32 ? e_end - c0 : 32;
+  };
+  // Loads are unconditional (lanes past the tile read edge 0) so that no
+  // select waits on them; the dz part zeroes those lanes.
+  auto load_col = [&](Tile& t) {
+    const int e = t.valid ? t.eid : 0;
+    t.jn = a.col[e];
+    t.dn = a.dst[e];
+  };
+  Tile tA, tB;   // the first two rounds' tiles, their ids on the way with the weights
+  locate(pr, tA);
+  load_col(tA);
+  locate(4 + pr, tB);
+  load_col(tB);
   stage_wait();
   __syncthreads();   // W2^T and the layer-1 weights are in LDS
 
-  __shared__ int rps[EG_NB + 1];
   __shared__ int slot_cnt[4];
   unsigned char* myslot = slots + pr * G::SLOT;
   // A operands of the z1 product, built each round from the fp32 weights in
@@ -805,49 +835,17 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
     f1 = pack_frag<__bf16>(v1);
   };
 
-  // a tile of the current block: 32 consecutive edges of the block's edge
-  // range (destinations d0 .. d0 + nd - 1, rows in order), which may span
-  // several destinations: the first and last of them, the first edge, the
-  // lane's edge, its source and its destination
-  struct Tile {
-    int i0, i1, c0, eid, cnt, jn, dn;   // graph indices are int32
-    bool has, valid;
-  };
   // the operands of a tile: gathered row, the half's rows of U_i, mask bits, node attribute rows
   struct Ops {
     frag hB[SKD], UA[KTH][SKD];
     uint32_t m1[MW1], m2[MW2];
     float ri[4], rj[4];
   };
-  int d0 = 0;
-  int ntile = 0;
-  int nd = 0;
-  auto locate = [&](int tau, Tile& t) {
-    t.has = tau < ntile;
-    t.i0 = t.i1 = d0; t.c0 = 0; t.eid = 0; t.cnt = 0; t.valid = false;
-    if (!t.has) return;
-    const int pe = rps[nd];
-    t.c0 = rps[0] + tau * 32;
-    t.eid = t.c0 + l32;
-    t.valid = t.eid < pe;
-    t.cnt = pe - t.c0 < 32 ? pe - t.c0 : 32;
-    // destination of an edge of the block: the number of row ends at or below it
-    const int re = lane < nd ? rps[lane + 1] : 0x7fffffff;
-    t.i0 = d0 + __popcll(__ballot(re <= t.c0));
-    t.i1 = d0 + __popcll(__ballot(re <= t.c0 + t.cnt - 1));
-  };
-  // Loads are unconditional (lanes past the tile read edge 0) so that no
-  // select waits on them; the dz part zeroes those lanes.
-  auto load_col = [&](Tile& t) {
-    const int e = t.valid ? t.eid : 0;
-    t.jn = a.col[e];
-    t.dn = a.dst[e];
-  };
   // the gathered row and the half's rows of U_i (issued as soon as the
   // previous tile's products have read those registers) ...
   auto load_uh = [&](const Tile& t, Ops& o) {
     if (!t.has) return;
-    const int i = __builtin_amdgcn_readfirstlane(t.i0);   // the tile's first destination
+    const int i = __builtin_amdgcn_readfirstlane(t.dn);   // the tile's first destination
     const unsigned char* ub = a.U + (size_t)i * (H2 * DL * 2);   // fragment order
     const unsigned char* hr = a.h_in + (size_t)t.jn * DL * 2;
 #pragma unroll
@@ -957,12 +955,12 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
     f32x16 acc[KTH];
 #pragma unroll
     for (int q = 0; q < KTH; ++q) acc[q] = f32x16{};
-    for (int i = t.i0; i <= t.i1; ++i) {
+    const int i0 = __builtin_amdgcn_readfirstlane(t.dn);
+    for (int i = i0;;) {
       const bool mine = t.dn == i;
-      if (__ballot(mine) == 0) continue;   // a destination without edges
-      if (i != t.i0) {
+      if (i != i0) {
         // a scalar row base and 32-bit lane offsets
-        const unsigned char* ub = a.U + (size_t)__builtin_amdgcn_readfirstlane(i) * (H2 * DL * 2);
+        const unsigned char* ub = a.U + (size_t)i * (H2 * DL * 2);
 #pragma unroll
         for (int q = 0; q < KTH; ++q)
 #pragma unroll
@@ -976,6 +974,9 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
       for (int q = 0; q < KTH; ++q)
 #pragma unroll
         for (int s = 0; s < SKD; ++s) acc[q] = M::mma(o.UA[q][s], hBm[s], acc[q]);
+      const uint64_t later = __ballot(t.valid && t.dn > i);   // destinations ascend over the lanes
+      if (later == 0) break;
+      i = __builtin_amdgcn_readlane(t.dn, __builtin_ctzll(later));
     }
     load_uh(nxt, o);   // the products above have read these registers
     // da2 = dz [z > 0] for the half's positions n = 16 kt + i (frags s = n / EPL)
@@ -1101,27 +1102,13 @@ __global__ __launch_bounds__(512, 1) void k_bwd_edge_agg(EdgeGradArgs g) {
     lds_barrier();   // slots are free for the next round
   };
 
-  const int64_t nblk = (a.n_dst + g.nb - 1) / g.nb;
-  for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    d0 = (int)(blk * g.nb);
-    nd = (int)(a.n_dst - d0 < g.nb ? a.n_dst - d0 : g.nb);
-    if (wv == 0 && lane <= nd) rps[lane] = a.row_ptr[d0 + lane];
-    lds_barrier();
-    ntile = (rps[nd] - rps[0] + 31) / 32;
-    Tile tA, tB;
-    locate(pr, tA);
-    load_col(tA);
-    locate(4 + pr, tB);
-    load_col(tB);
-    load_uh(tA, op);
-    load_attr(tA, op);
-    load_m2(tA, op);
-    load_m1(tA, op);
-    for (int r0 = 0; r0 < ntile; r0 += 8) {
-      round(r0, tA, tB);
-      if (r0 + 4 < ntile) round(r0 + 4, tB, tA);
-    }
-    lds_barrier();   // the block's row pointers are read until every wave is done
+  load_uh(tA, op);
+  load_attr(tA, op);
+  load_m2(tA, op);
+  load_m1(tA, op);
+  for (int r0 = 0; r0 < ntile; r0 += 8) {
+    round(r0, tA, tB);
+    if (r0 + 4 < ntile) round(r0 + 4, tB, tA);
   }
   // ---- partial sums of this workgroup (stored positions mapped back to k, j)
   float* o2 = g.p_w2 + (size_t)blockIdx.x * (H2 * H1 + H2);
@@ -2984,17 +2971,19 @@ dsmp_status run_edge_grads_fused(dsmp_handle* h, const EdgeGradArgs& eg, int cap
   if (st != DSMP_OK) return st;
   int per_cu = 0;
   DSMP_HIP(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kf, G::NT, G::LDS));
-  // Blocks as even as they come: every workgroup of the chip gets one of up to
-  // EG_NB destinations, or the same number of them.  Each block starts with three
-  // loads that wait for one another and ends with a part-filled round; blocks of
-  // 16 gave 900 destinations to 57 workgroups: 27 -> 17 us there, 2,048 of degree
-  // 13 and 21 29 -> 23 and 35 -> 25, 40,000 of degree 27 311 -> 301, and at d = 32
-  // 40,000 of degree 23 168 -> 159.
+  // The edges are split evenly over the workgroups of the chip, by tiles; fewer
+  // workgroups with the same number of tiles each where that is one round or less
+  // (each leaves partial sums to be added up).  Split evenly by destinations, rows
+  // of uneven length left workgroups idle: backward of 6,000 destinations, the
+  // first 1,500 of 200 edges and the others of few, 230 -> 153 us at d = 32 and 426
+  // -> 316 at d = 64; of even ones 8,192 of degree 40 118 -> 112 and 249 -> 239, 900
+  // of degree 20 41.1 -> 40.6 and 69.0 -> 68.2, 100,000 of 30 1,080 -> 1,036 and 2,161
+  // -> 2,088.
   const int64_t slots = std::max<int64_t>(1, std::min<int64_t>((int64_t)h->n_cu * std::max(per_cu, 1), cap));
-  const int64_t rounds = std::max<int64_t>(1, ceil_div(dz.n_dst, slots * EG_NB));
+  const int64_t ntile = ceil_div(dz.E, 32);
   EdgeGradArgs ea = eg;
-  ea.nb = (int)std::max<int64_t>(1, ceil_div(dz.n_dst, slots * rounds));
-  const int64_t grid = std::min<int64_t>(ceil_div(dz.n_dst, ea.nb), slots);
+  ea.unit = 32 * (int)(ntile <= 4 * slots ? ceil_div(ntile, slots) : 1);
+  const int64_t grid = std::min<int64_t>(ceil_div(dz.E, ea.unit), slots);
   ProfScope prof(h, DSMP_K_DZ);
   hipLaunchKernelGGL(kf, dim3((unsigned)grid), dim3(G::NT), G::LDS, s, ea);
   DSMP_LAUNCHED(h, "fused edge gradients");

@@ -268,6 +268,42 @@ def test_node_terms_sliced_sums(env, algo, shape):
     _check_backward(c, "E=%d" % c.col.size)
 
 
+@pytest.mark.parametrize("shape", ["bf16_32", "bf16_64"])
+@pytest.mark.parametrize("sizes,gap", [((2,), 0), ((6, 2), 90), ((5, 3, 2, 2), 3000), ((12,), 5), ((190, 3, 40, 2), 700)])
+def test_backward_fused_edge_ranges(env, shape, sizes, gap):
+    """The fused edge gradients deal the edges out, not the destinations: cliques
+    of the given sizes (2 to 37,000 edges, whole and part-filled tiles, tiles of
+    one destination and of many) with `gap` destinations without edges after
+    each, which a tile may span."""
+    dm, lib, torch = env
+    announce("fused edge ranges", shape, sizes, gap)
+    dtype, d, h1, h2 = SHAPES[shape]
+    g = np.random.default_rng(sum(sizes) + gap)
+    at, rows = [], []
+    for k, m in enumerate(sizes):
+        rows += list(range(len(at), len(at) + m))
+        at += [[k, 1.0]] * m + [[1000.0 + 2 * (k * gap + i), 5.0] for i in range(gap)]
+    pos = (np.array(at) + 0.01 * g.uniform(0, 1, (len(at), 2))).astype(np.float32)
+    n = pos.shape[0]
+    attr = np.concatenate([g.uniform(0, 1, (n, 2)), g.uniform(0, 2, (n, 1))], 1).astype(np.float32)
+    h = bf16_round(g.normal(0, 1, (n, d)).astype(np.float32))
+    G = np.zeros((n, d), np.float32)
+    G[rows] = g.normal(0, 1, (len(rows), d))
+    c = Case(env, pos, attr, h, n, 0.1, 0, layer_params(g, d, 6, h1, h2, dtype), dtype, 2, d, h1, h2, G=G,
+             rows=np.array(rows))
+    assert c.col.size == sum(m * (m - 1) for m in sizes)
+    lib.dsmp_set_edge_algorithm(dm.EDGE_AGGREGATE)
+    try:
+        c.forward()
+        gh, grads = c.backward()
+    finally:
+        lib.dsmp_set_edge_algorithm(dm.EDGE_AUTO)
+    ref = c.oracle_backward()
+    assert rel_err(gh, ref["grad_h"], ref["allow"]["grad_h"]) <= TOL["bf16"]
+    for k in GRAD_KEYS:
+        assert rel_err(grads[k], ref[k], ref["allow"][k]) <= TOL["bf16"], k
+
+
 def test_backward_workspace_few_edges(env):
     """The backward of a d = 128 layer with a handful of edges (its da1 pass
     writes four partial sums, more than one per 64 edges) stays within the
