@@ -578,7 +578,7 @@ __device__ __forceinline__ void select_cap_bits(const uint64_t* key, Pay pay, ui
 // bracketed, lo < cap-th smallest <= hi, and probed between them by
 // interpolation on the counts (two or three probes bring a bracket of 90 down to
 // a shell of a few, where the bits above decide one at a time, 25 or so: 575 ->
-// 449 us for 262,144 rows of 90 with the shorter candidate walk); the
+// 414 us for 262,144 rows of 90, walk and tests included); the
 // keys of a bracket of at most SEL_RANK are then ranked exactly, both words,
 // one per lane.  Equal or nearly equal keys that no bracket of that size
 // separates (after SEL_PROBES) are left to the bits.  frac: the share of the

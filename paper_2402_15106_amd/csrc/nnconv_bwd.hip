@@ -3025,9 +3025,11 @@ namespace dsmp {
 // reading U once instead of twice is worth passing da2 (256 bytes per edge,
 // written once and read twice) and the attributes through memory: U past the
 // 256 MB last-level cache, and at most 22 edges per destination.  Layer
-// forward and backward, fused against this: 100,000 nodes of 10.8 edges 2620 and
-// 2410 us; 40,000 of 11.9, 16.8, 21.8, 27.2: 1120 and 1050, 1199 and 1150, 1283
-// and 1266, 1388 and 1389; 30,011 of 21: 995 and 971; 8,192 of 13.2: 292 and 303.
+// forward and backward, fused against this: 100,000 nodes of 11.5 and 23.7 edges
+// 2,571 and 2,360, 3,017 and 2,870 us; 40,000 of 11.9, 16.8, 21.7, 27.1: 1,090 and
+// 1,014, 1,162 and 1,110, 1,244 and 1,210, 1,323 and 1,317; 16,500 of 15.7 and 23.5:
+// 516 and 500, 561 and 561; 8,192 of 12.3: 284 and 279.  Both lines lie inside what
+// is faster: past them the gain is 3 % and less.
 bool dz_with_m(const dsmp_layer_desc& d, bool agg, int64_t n_dst, int64_t E) {
   if (!agg || d.dtype != DSMP_BF16) return false;
   if (d.d == 128) return d.h1 == 256 && d.h2 == 256;
